@@ -153,7 +153,10 @@ extern "C" sd_status sd_autotune(const sd_params* p, int64_t n, int32_t precisio
     std::vector<Cand> res;
     for (const sd_kernel_config& c : candidates(precision, n)) {
         if (check_config(precision, c) != SD_OK) continue;
-        if ((st = sd_set_kernel_config(precision, &c))) break;
+        // (the automatic choice is timed as the library runs it, not forced)
+        const bool automatic = same_config(c, default_config(precision, n));
+        if (automatic) set_tuned_config(precision, n, nullptr);
+        if ((st = sd_set_kernel_config(precision, automatic ? nullptr : &c))) break;
         if ((st = mobility_apply(p, n, pos, frc, vel, precision, stream))) break;
         (void)hipEventRecord(e0, hs);
         for (int r = 0; r < 3; ++r)
@@ -174,8 +177,10 @@ extern "C" sd_status sd_autotune(const sd_params* p, int64_t n, int32_t precisio
     if (st) return st;
     if (res.empty()) return fail(SD_EUNSUPPORTED, "no candidate configuration ran");
     std::sort(res.begin(), res.end(), [](const Cand& a, const Cand& b) { return a.ms < b.ms; });
-    set_tuned_config(precision, n, res[0].c);
+    // (nothing is installed where the automatic choice is the fastest: it may
+    // run kernels that no configuration names)
     const sd_kernel_config d = default_config(precision, n);
+    set_tuned_config(precision, n, same_config(res[0].c, d) ? nullptr : &res[0].c);
     double default_ms = -1.0;   // -1: the automatic choice did not run
     for (const Cand& r : res)
         if (same_config(r.c, d)) default_ms = r.ms;

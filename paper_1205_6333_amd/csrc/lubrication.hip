@@ -469,7 +469,6 @@ sd_status sd_run_lub(const sd_params* p, const sd_lub* lub, int64_t n, double* x
         (st = ws_get(WS_STAGE, rec * (size_t)n, &stage)) ||
         (st = ws_get(WS_LUB_F, rec * (size_t)n, &F4)))
         return st;
-    const double mu0 = 1.0 / (6.0 * M_PI * p->eta * p->a);
     // per step: forces with the correction (written straight into the force
     // records of the pair kernel), pair kernel, then merge + integrate, which
     // also stages the new positions for the next step
@@ -486,15 +485,9 @@ sd_status sd_run_lub(const sd_params* p, const sd_lub* lub, int64_t n, double* x
         // Euler: x += dt v, v_prev = v;  AB2: x += dt (3/2 v - 1/2 v_prev), v_prev = v
         const int mode = (integrator == SD_EULER) ? 0 : (k == 0 ? 1 : 2);
         const bool next = s + 1 < steps;
-        e = f64 ? launch_merge_integrate_f64((double*)partial, L.splits, (int)n, (const double4*)F4,
-                                             mu0, x, mode ? v_prev : nullptr,
-                                             mode ? nullptr : v_prev, dt, mode,
-                                             next ? (double4*)stage : nullptr, hs)
-                : launch_merge_integrate_f32((double*)partial, L.splits, (int)n, (const float4*)F4,
-                                             mu0, x, mode ? v_prev : nullptr,
-                                             mode ? nullptr : v_prev, dt, mode,
-                                             next ? (float4*)stage : nullptr, box_side(p), hs);
-        if (e != hipSuccess) return fail(SD_EDEVICE, "integrate launch: %s", hipGetErrorString(e));
+        if ((st = finish_step(p, n, F4, precision, (double*)partial, L, x, mode ? v_prev : nullptr,
+                              mode ? nullptr : v_prev, dt, mode, next ? stage : nullptr, hs)))
+            return st;
     }
     return SD_OK;
 }

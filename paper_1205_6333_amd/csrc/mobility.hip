@@ -14,6 +14,7 @@
 // evaluated in FP64 on a rarely taken branch.  SD_FP64 runs the same loop in
 // double.
 #include "pair_terms.h"
+#include "premise.h"
 #include "sd_internal.h"
 #include "sym_chunk_asm.h"
 
@@ -167,20 +168,7 @@ __device__ __forceinline__ void near_diff(const LaneF32& L, const float4 pj, int
 // on the rare FP64 near-pair branch only, by the evaluation of row min(i, j).
 __device__ unsigned long long g_premise[2];
 
-// Called by the lanes active at that point, each with the class of its pair
-// (PREMISE_OK for none): one atomic add per class and call, by one lane, for
-// the whole wave (a dense suspension meets thousands of such pairs per
-// product, and atomics on one address serialise).
-__device__ __forceinline__ void count_premise(int cls)
-{
-    const uint64_t sub = __builtin_amdgcn_ballot_w64(cls == PREMISE_SUB2A);
-    const uint64_t co = __builtin_amdgcn_ballot_w64(cls == PREMISE_COINCIDENT);
-    if ((sub | co) == 0) return;
-    const uint64_t act = __builtin_amdgcn_ballot_w64(true);
-    if ((int)(threadIdx.x & 63) != __builtin_ctzll(act)) return;
-    if (sub) atomicAdd(&g_premise[0], (unsigned long long)__builtin_popcountll(sub));
-    if (co) atomicAdd(&g_premise[1], (unsigned long long)__builtin_popcountll(co));
-}
+__device__ __forceinline__ void count_premise(int cls) { count_premise(g_premise, cls); }
 
 // Per-lane counts, added for the wave with one atomic add per class (all
 // lanes of the wave call it).
@@ -1912,16 +1900,21 @@ __global__ void k_premise_clear(unsigned long long* c)
     if (threadIdx.x < 2) c[threadIdx.x] = 0ull;
 }
 
+hipError_t premise_counters(unsigned long long** counters)
+{
+    return hipGetSymbolAddress((void**)counters, HIP_SYMBOL(g_premise));
+}
+
 hipError_t premise_counts(int64_t* sub2a, int64_t* coincident, bool reset, hipStream_t st)
 {
     // the counters of the current device (each device holds its own copy)
-    void* dev = nullptr;
-    hipError_t e = hipGetSymbolAddress(&dev, HIP_SYMBOL(g_premise));
+    unsigned long long* dev = nullptr;
+    hipError_t e = premise_counters(&dev);
     if (e != hipSuccess) return e;
     unsigned long long h[2] = { 0ull, 0ull };
     if ((e = hipMemcpyAsync(h, dev, sizeof h, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
     if (reset) {
-        hipLaunchKernelGGL(k_premise_clear, dim3(1), dim3(64), 0, st, (unsigned long long*)dev);
+        hipLaunchKernelGGL(k_premise_clear, dim3(1), dim3(64), 0, st, dev);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;

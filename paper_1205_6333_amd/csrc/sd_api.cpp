@@ -3,6 +3,7 @@
 #include "sd.h"
 #include "sd_internal.h"
 #include "sd_host.h"
+#include "wave_sym.h"
 
 #include <hip/hip_runtime.h>
 
@@ -256,8 +257,9 @@ sd_kernel_config default_config(int32_t prec, int64_t n)
     return c;
 }
 
-sd_kernel_config choose_config(int32_t prec, int64_t n)
+sd_kernel_config choose_config(int32_t prec, int64_t n, bool* automatic)
 {
+    if (automatic) *automatic = true;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         const ConfigTable& t = g_cfg[prec];
@@ -278,15 +280,21 @@ sd_kernel_config choose_config(int32_t prec, int64_t n)
         }
         // a forced or tuned variant-2 shape whose j-side workspace for this n
         // exceeds the cap falls back to the automatic configuration
-        if (have && !(c.variant == 2 && !sym_fits(n, c.block * c.ilp))) return c;
+        if (have && !(c.variant == 2 && !sym_fits(n, c.block * c.ilp))) {
+            if (automatic) *automatic = false;
+            return c;
+        }
     }
     return default_config(prec, n);
 }
 
-void set_tuned_config(int32_t prec, int64_t n, const sd_kernel_config& c)
+void set_tuned_config(int32_t prec, int64_t n, const sd_kernel_config* c)
 {
     std::lock_guard<std::mutex> lk(g_mu);
-    g_cfg[prec].tuned[size_class(n)] = c;
+    if (c)
+        g_cfg[prec].tuned[size_class(n)] = *c;
+    else
+        g_cfg[prec].tuned.erase(size_class(n));
 }
 
 sd_status check_config(int32_t prec, const sd_kernel_config& c)
@@ -377,26 +385,72 @@ sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* f
     hipEvent_t ev;
     prof_begin(st, &ev);
     hipError_t e;
-    if (prec == SD_FP64)
+    if (L.variant == 3)
+        e = launch_wave_f64(L, p->tensor, (const double4*)pos, (const double4*)frc, (int)n, pc,
+                            partial, st);
+    else if (prec == SD_FP64)
         e = launch_pair_f64(L, p->tensor, (const double4*)pos, (const double4*)frc, (int)n, pc,
                             partial, st);
     else
         e = launch_pair_f32(L, p->tensor, L.acc, (const float4*)pos, (const float4*)frc, x64,
                             (int)n, pc, partial, st);
     prof_end(st, ev);
-    const bool fuse = vel && prec != SD_FP64 && L.variant == 2;
+    if (e == hipSuccess && L.variant == 3 && vel)
+        e = launch_wave_fold_f64(L, (int)n, pc, partial, (const double4*)frc, vel, nullptr,
+                                 nullptr, nullptr, 0.0, 0, nullptr, st);
+    const bool fuse = vel && (L.variant == 2 || L.variant == 3);
     if (e == hipSuccess && prec != SD_FP64)
         e = launch_pair_fold(L, p->tensor, (const float4*)pos, (const float4*)frc, x64, (int)n, pc,
                              partial, st, 1.0 / (6.0 * M_PI * p->eta * p->a),
-                             fuse ? vel : nullptr);
+                             vel);
     if (e == hipSuccess && fuse && merged) *merged = true;
     if (e != hipSuccess) return fail(SD_EDEVICE, "pair kernel launch: %s", hipGetErrorString(e));
     return SD_OK;
 }
 
+sd_status finish_step(const sd_params* p, int64_t n, const void* frc, int32_t prec,
+                      const double* partial, const PairLaunch& L, double* x, double* v_prev,
+                      double* v_out, double dt, int mode, void* pos_next, hipStream_t st)
+{
+    const double mu0 = 1.0 / (6.0 * M_PI * p->eta * p->a);
+    hipError_t e;
+    if (L.variant == 3)
+        e = launch_wave_fold_f64(L, (int)n, pair_const(p), partial, (const double4*)frc, nullptr,
+                                 x, v_prev, v_out, dt, mode, (double4*)pos_next, st);
+    else if (prec == SD_FP64)
+        e = launch_merge_integrate_f64(partial, L.splits, (int)n, (const double4*)frc, mu0, x,
+                                       v_prev, v_out, dt, mode, (double4*)pos_next, st);
+    else
+        e = launch_merge_integrate_f32(partial, L.splits, (int)n, (const float4*)frc, mu0, x,
+                                       v_prev, v_out, dt, mode, (float4*)pos_next, box_side(p),
+                                       st);
+    if (e != hipSuccess) return fail(SD_EDEVICE, "integrate launch: %s", hipGetErrorString(e));
+    return SD_OK;
+}
+
+PairLaunch plan_wave(int64_t n, int ilp)
+{
+    PairLaunch L{};
+    L.variant = 3;
+    L.block = 256;
+    L.ilp = ilp;
+    L.cus = device_cus();
+    // two rounds of four waves per SIMD (one and four rounds time alike at
+    // N = 8192 and 16384: the chunks are small, and more rounds mean more
+    // split rows for the fold to read)
+    L.jchunk = 32 * L.cus;
+    L.splits = wave_shape_of(L, (int)n).splits + 1;
+    return L;
+}
+
 PairLaunch plan_pair(int32_t prec, int64_t n)
 {
-    const sd_kernel_config c = choose_config(prec, n);
+    bool automatic = false;
+    const sd_kernel_config c = choose_config(prec, n, &automatic);
+    if (automatic && prec == SD_FP64 && n >= WAVE_F64_MIN_N) {
+        const PairLaunch W = plan_wave(n, n >= WAVE_ILP2_MIN_N ? 2 : 1);
+        if (partial_bytes(W, n) <= SYM_WORKSPACE_CAP) return W;
+    }
     PairLaunch L = shape_pair_launch((int)n, c.variant, c.block, c.splits, c.ilp, device_cus());
     L.acc = (prec == SD_FP64) ? 0 : c.kahan_block;
     if (prec == SD_FP32_PLAIN) L.acc = 0;
@@ -406,6 +460,10 @@ PairLaunch plan_pair(int32_t prec, int64_t n)
 size_t partial_bytes(const PairLaunch& L, int64_t n)
 {
     if (L.variant == 2) return sym_workspace_bytes(L, n);
+    if (L.variant == 3) {
+        const WaveShape sh = wave_shape_of(L, (int)n);
+        return wave_jpart_offset(sh, n) + wave_jpart_bytes(sh, sizeof(double));
+    }
     return (size_t)L.splits * 3 * (size_t)n * sizeof(double);
 }
 
@@ -538,17 +596,8 @@ static sd_status step_impl(const sd_params* p, int64_t n, double* x, const void*
                        hs)))
         return st;
     const int mode = (integrator == SD_EULER) ? 0 : (step_index == 0 ? 1 : 2);
-    const double mu0 = 1.0 / (6.0 * M_PI * p->eta * p->a);
-    if (prec == SD_FP64)
-        e = launch_merge_integrate_f64(partial, L.splits, (int)n, (const double4*)force, mu0, x,
-                                       v_prev, v_out, dt, mode,
-                                       stage_next ? (double4*)pos_stage : nullptr, hs);
-    else
-        e = launch_merge_integrate_f32(partial, L.splits, (int)n, (const float4*)force, mu0, x,
-                                       v_prev, v_out, dt, mode,
-                                       stage_next ? (float4*)pos_stage : nullptr, box_side(p), hs);
-    if (e != hipSuccess) return fail(SD_EDEVICE, "integrate launch: %s", hipGetErrorString(e));
-    return SD_OK;
+    return finish_step(p, n, force, prec, partial, L, x, v_prev, v_out, dt, mode,
+                       stage_next ? pos_stage : nullptr, hs);
 }
 
 static sd_status check_step_args(const sd_params* p, int64_t n, const double* x, const void* force,

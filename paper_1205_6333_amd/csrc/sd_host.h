@@ -49,18 +49,40 @@ constexpr size_t SYM_WORKSPACE_CAP = (size_t)1 << 30;
 // Smallest n for which the automatic configuration takes variant 2.
 constexpr int64_t SYM_MIN_N = 16384;
 bool sym_fits(int64_t n, int block);
-sd_kernel_config choose_config(int32_t prec, int64_t n);
-void set_tuned_config(int32_t prec, int64_t n, const sd_kernel_config& c);
+// Automatic FP64 products of at least WAVE_F64_MIN_N particles take the
+// wave-symmetric kernel (variant 3) while its workspace stays within the cap,
+// with two particles per lane from WAVE_ILP2_MIN_N on (one per lane gives
+// twice the waves of a small product; two share each hand-over and each read
+// of j).  Microseconds per mobility_apply, one-sided kernel / one / two
+// particles per lane: N = 1024 16.9 / 14.3 / 16.4, 2000 18.9 / 14.2 / -,
+// 3001 27.6 / 18.2 / 20.0, 4000 34.5 / 25.6 / 24.5, 6000 72.6 / 46.0 / 39.7,
+// 16384 301 / 246 / 200, 40000 1730 / - / 1107.
+constexpr int64_t WAVE_F64_MIN_N = 1024;
+constexpr int64_t WAVE_ILP2_MIN_N = 3500;
+// The configuration for n particles; *automatic (may be null) receives whether
+// it is the automatic choice (nothing forced, no tuned shape for the size).
+sd_kernel_config choose_config(int32_t prec, int64_t n, bool* automatic = nullptr);
+// Tuned shape of n's size class (null: none, the automatic choice applies).
+void set_tuned_config(int32_t prec, int64_t n, const sd_kernel_config* c);
 sd_status check_config(int32_t prec, const sd_kernel_config& c);
 
 PairConst pair_const(const sd_params* p);
 PairLaunch plan_pair(int32_t prec, int64_t n);
+// a wave-symmetric launch (variant 3) with ilp particles per lane
+PairLaunch plan_wave(int64_t n, int ilp);
 size_t partial_bytes(const PairLaunch& L, int64_t n);
 // vel (may be null): for the pair-symmetric kernel the product is finished
 // here (the fold merges into vel; *merged is set), else the caller merges.
 sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* frc,
                    const double* x64, int32_t prec, double* partial, const PairLaunch& L,
                    hipStream_t st, double* vel = nullptr, bool* merged = nullptr);
+
+// One time step's end: split rows -> v, positions and history (mode as
+// launch_merge_integrate_*), and the staged copy for the next pair kernel.
+// Enqueue after run_pair (without vel).
+sd_status finish_step(const sd_params* p, int64_t n, const void* frc, int32_t prec,
+                      const double* partial, const PairLaunch& L, double* x, double* v_prev,
+                      double* v_out, double dt, int mode, void* pos_next, hipStream_t st);
 
 void batch_release_graphs();
 void run_graphs_release();

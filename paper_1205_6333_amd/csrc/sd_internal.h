@@ -65,11 +65,13 @@ constexpr double NEAR_EPS = 1e-3;
 PairConst make_pair_const(double a, double eta, int tensor, int overlap, double box);
 
 struct PairLaunch {
-    int variant;   // 0 LDS tiles, 1 scalar-cache j stream, 2 pair symmetry (FP32 only)
+    int variant;   // 0 LDS tiles, 1 scalar-cache j stream, 2 pair symmetry (FP32 only),
+                   // 3 wave-symmetric (automatic choice only)
     int block;     // threads per work-group
     int splits;    // number of partial rows written (variants 0/1: j-range splits)
     int jchunk;    // variants 0/1: particles j per split (multiple of block);
-                   // variant 2: the requested split count the schedule was cut from
+                   // variant 2: the requested split count the schedule was cut from;
+                   // variant 3: the waves the schedule was cut for
     int ilp;       // i per lane
     int acc;       // FP32 accumulation: 0 plain, k = Kahan per k terms
     int cus;       // variant 2: compute units the schedule was cut for
@@ -136,6 +138,16 @@ hipError_t launch_pair_fold(const PairLaunch& L, int tensor, const float4* pos, 
                             const double* x64, int n, const PairConst& pc, double* partial,
                             hipStream_t st, double mu0 = 0.0, double* vel = nullptr);
 
+// Variant 3 (wave_sym.h): the FP64 pair kernel, and the fold that adds its
+// partials and writes velocities (vel given) or does the time step (vel null;
+// arguments as launch_merge_integrate_f64).
+hipError_t launch_wave_f64(const PairLaunch& L, int tensor, const double4* pos, const double4* frc,
+                           int n, const PairConst& pc, double* partial, hipStream_t st);
+hipError_t launch_wave_fold_f64(const PairLaunch& L, int n, const PairConst& pc,
+                                const double* partial, const double4* frc, double* vel, double* x,
+                                double* v_prev, double* v_out, double dt, int mode,
+                                double4* pos_next, hipStream_t st);
+
 // v_i = mu0 F_i + sum_s partial_s (fixed order).
 // Read the current device's counts of pairs with 0 < r < 2a and r = 0 met by
 // the product kernels (stream-ordered; synchronises st), zeroing them if reset.
@@ -169,6 +181,15 @@ hipError_t launch_adjoint_f32(const PairLaunch& L, int tensor, const float4* pos
 hipError_t launch_adjoint_f64(const PairLaunch& L, int tensor, const double4* pos,
                               const double4* frc, const double4* lam, int n, const PairConst& pc,
                               double* partial, double* partial_f, hipStream_t st);
+// The wave-symmetric adjoint pass (wave_adjoint.hip): pair kernel and fold.  ws:
+// wave_adjoint_bytes(L, n) bytes.  lam64 null: gpos and gforce (either may be
+// null) are written; else one step of the Euler loop: gforce and lam64 are
+// updated and lam (then written) receives the record of the new lam64.
+size_t wave_adjoint_bytes(const PairLaunch& L, int64_t n);
+hipError_t launch_wave_adjoint(const PairLaunch& L, int tensor, bool f64, const void* pos,
+                               const void* frc, void* lam, const double* x64, int n,
+                               const PairConst& pc, void* ws, double* lam64, double dt,
+                               double* gpos, double* gforce, hipStream_t st);
 // out[3i+k] = sum_s partial (no self term); accumulate != 0 adds scale*sum to out.
 hipError_t launch_sum_partials(const double* partial, int splits, int n, double* out, double scale,
                                int accumulate, hipStream_t st);
