@@ -15,6 +15,7 @@
 #include "sd.h"
 #include "sd_host.h"
 #include "sd_internal.h"
+#include "wave_sym.h"
 
 #include <algorithm>
 #include <cmath>
@@ -480,14 +481,33 @@ static PairLaunch plan_adjoint(int32_t prec, int64_t n)
     return L;
 }
 
-// One adjoint pass: the fused pair kernel, then the merge (see k_adjoint_merge).
+// One adjoint pass: the pair kernel, then the merge (see k_adjoint_merge).  In
+// the Euler loop (lam64 given) lam4 holds the record of lam64 on entry; the
+// wave-symmetric pass leaves that of the new lam64 there (*next_lam4 set).
 static sd_status adjoint_pass(const sd_params* p, int64_t n, const void* pos, const void* frc,
-                              const void* lam4, const double* x64, int32_t prec, double* lam64,
-                              double dt, double* gpos, double* gforce, hipStream_t hs)
+                              void* lam4, const double* x64, int32_t prec, double* lam64,
+                              double dt, double* gpos, double* gforce, hipStream_t hs,
+                              bool* next_lam4 = nullptr)
 {
     sd_status st;
-    const PairLaunch L = plan_adjoint(prec, n);
     void* partial = nullptr;
+    // each pair once wherever the j-side workspace fits (N = 50000 or so);
+    // microseconds per pass, one-sided / each pair once: FP64 N = 64 43 / 17,
+    // 3001 134 / 29, 8192 352 / 125; FP32 N = 64 52 / 16, 3001 58 / 24, 8192
+    // 131 / 86
+    const PairLaunch W = plan_wave(n, 1);
+    const size_t wb = wave_adjoint_bytes(W, n);
+    if (wb <= SYM_WORKSPACE_CAP) {
+        if ((st = ws_get(WS_ADJ_PARTIAL, wb, &partial))) return st;
+        const hipError_t e = launch_wave_adjoint(W, p->tensor, prec == SD_FP64, pos, frc, lam4,
+                                                 x64, (int)n, pair_const(p), partial, lam64, dt,
+                                                 gpos, gforce, hs);
+        if (e != hipSuccess) return fail(SD_EDEVICE, "adjoint launch: %s", hipGetErrorString(e));
+        if (next_lam4) *next_lam4 = true;
+        return SD_OK;
+    }
+    if (next_lam4) *next_lam4 = false;
+    const PairLaunch L = plan_adjoint(prec, n);
     const size_t pb = partial_bytes(L, n);
     if ((st = ws_get(WS_ADJ_PARTIAL, 2 * pb, &partial))) return st;
     double* pp = (double*)partial;
@@ -535,8 +555,9 @@ sd_status mobility_adjoint(const sd_params* p, int64_t n, const void* pos, const
         return st;
     if (grad_force && (uintptr_t)grad_force % 8)
         return fail(SD_EALIGN, "grad_force is not 8-byte aligned");
-    return adjoint_pass(p, n, pos, force, lam, nullptr, precision, nullptr, 0.0, grad_pos,
-                        grad_force, (hipStream_t)stream);
+    // (a single product only reads lam)
+    return adjoint_pass(p, n, pos, force, const_cast<void*>(lam), nullptr, precision, nullptr, 0.0,
+                        grad_pos, grad_force, (hipStream_t)stream);
 }
 
 sd_status sd_run_adjoint(const sd_params* p, int64_t n, const double* x0, const void* force,
@@ -599,6 +620,7 @@ sd_status sd_run_adjoint(const sd_params* p, int64_t n, const double* x0, const 
     double* lam = grad_x0;
     double* T = (double*)traj;
     const int64_t nseg = (steps + E - 1) / E;
+    bool have_lam4 = false;
     for (int64_t seg = nseg - 1; seg >= 0; --seg) {
         const int64_t k0 = seg * E;
         const int64_t k1 = std::min(steps, k0 + E);
@@ -621,13 +643,13 @@ sd_status sd_run_adjoint(const sd_params* p, int64_t n, const double* x0, const 
             hipError_t e;
             e = f64 ? launch_pack_f64(xk, (double4*)pos, (int)n, hs)
                     : launch_pack_f32(xk, (float4*)pos, (int)n, hs);
-            if (e == hipSuccess)
+            if (e == hipSuccess && !have_lam4)
                 e = f64 ? launch_pack_f64(lam, (double4*)lam4, (int)n, hs)
                         : launch_pack_f32(lam, (float4*)lam4, (int)n, hs);
             if (e != hipSuccess) return fail(SD_EDEVICE, "pack launch: %s", hipGetErrorString(e));
             // dL/dF += dt M(x_k) lam_{k+1};  lam_k = lam_{k+1} + dt d/dx [lam_{k+1} . M(x_k) F]
             if ((st = adjoint_pass(p, n, pos, force, lam4, f64 ? nullptr : xk, precision, lam, dt,
-                                   nullptr, grad_force, hs)))
+                                   nullptr, grad_force, hs, &have_lam4)))
                 return st;
         }
     }
