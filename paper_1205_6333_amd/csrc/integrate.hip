@@ -6,27 +6,6 @@
 
 namespace sd {
 
-// Fixed-point coordinate of a periodic box (q = x 2^32 / Lb mod 2^32, see
-// PairConst), returned as the bits of a float record.  qs = 2^32 / Lb.
-__device__ __forceinline__ float fixed_coord(double x, double qs)
-{
-    const long long t = (long long)rint(x * qs);
-    return __uint_as_float((unsigned int)(unsigned long long)t);
-}
-
-// FP32 record of a position: plain FP32 (qs = 0) or fixed point (qs > 0).
-__device__ __forceinline__ void put_pos(float4* p, int i, double a, double b, double c, double qs)
-{
-    if (qs > 0.0)
-        p[i] = make_float4(fixed_coord(a, qs), fixed_coord(b, qs), fixed_coord(c, qs), 0.0f);
-    else
-        p[i] = make_float4((float)a, (float)b, (float)c, 0.0f);
-}
-__device__ __forceinline__ void put_pos(double4* p, int i, double a, double b, double c, double)
-{
-    p[i] = make_double4(a, b, c, 0.0);
-}
-
 template <typename P4>
 __global__ void __launch_bounds__(256) k_stage(const double* __restrict__ x, P4* __restrict__ pos,
                                                int n, double qs)

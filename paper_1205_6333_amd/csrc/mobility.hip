@@ -104,15 +104,6 @@ __device__ __forceinline__ float far_i() { return PER ? 0.0f : SD_FAR_I; }
 template <bool PER>
 __device__ __forceinline__ float far_j() { return PER ? 0.0f : SD_FAR_J; }
 
-// FP32 coordinate difference a - b.  Periodic: a and b hold fixed-point bits;
-// the 32-bit wrapped difference is the nearest image in units of s.
-template <bool PER>
-__device__ __forceinline__ float pdiff(float a, float b)
-{
-    if (PER) return (float)(int)(__float_as_uint(a) - __float_as_uint(b));
-    return a - b;
-}
-
 // FP32 constants of the pair terms, held in VGPRs.  On gfx950 a VALU
 // instruction that reads an SGPR operand issues at half the rate of one that
 // reads VGPRs only (measured: 4.1 vs 2.2 cycles per wave instruction and
@@ -1373,31 +1364,6 @@ k_pair_f32_sym_asm(const float4* __restrict__ pos, const float4* __restrict__ fr
     L[1].c1 = -n1y;
     L[1].c2 = -n1z;
     sym_lanes_store<ILP, BLOCK>(L, n, ib, s, pc.alpha_sum, partial);
-}
-
-// FP64 difference x_i - x_j of a near pair (i: position xi of the FP32
-// record): from the FP64 positions when given (nearest image in a box), else
-// from the FP32 records (exact difference of floats, or the fixed-point
-// difference times s).
-template <bool PER>
-__device__ __forceinline__ void near_diff_v(float xi, float yi, float zi, int i, float4 pj, int jg,
-                                            const PairConst& pc, const double* __restrict__ x64,
-                                            double& d0, double& d1, double& d2)
-{
-    if (x64) {
-        d0 = x64[3 * (size_t)i + 0] - x64[3 * (size_t)jg + 0];
-        d1 = x64[3 * (size_t)i + 1] - x64[3 * (size_t)jg + 1];
-        d2 = x64[3 * (size_t)i + 2] - x64[3 * (size_t)jg + 2];
-        if (PER) nearest_image_d(pc, d0, d1, d2);
-    } else if (PER) {
-        d0 = (double)(int)(__float_as_uint(xi) - __float_as_uint(pj.x)) * pc.s_q;
-        d1 = (double)(int)(__float_as_uint(yi) - __float_as_uint(pj.y)) * pc.s_q;
-        d2 = (double)(int)(__float_as_uint(zi) - __float_as_uint(pj.z)) * pc.s_q;
-    } else {
-        d0 = (double)xi - (double)pj.x;
-        d1 = (double)yi - (double)pj.y;
-        d2 = (double)zi - (double)pj.z;
-    }
 }
 
 // Last split row of variant 2, one wave per run S of SYM_RUN particles

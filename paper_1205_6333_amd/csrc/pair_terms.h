@@ -47,6 +47,40 @@ __device__ __forceinline__ int near_term(const PairConst& pc, double d0, double 
     return r2 < 4.0 * pc.a * pc.a ? PREMISE_SUB2A : PREMISE_OK;
 }
 
+// FP32 coordinate difference a - b.  Periodic: a and b hold fixed-point bits;
+// the 32-bit wrapped difference is the nearest image in units of s.
+template <bool PER>
+__device__ __forceinline__ float pdiff(float a, float b)
+{
+    if (PER) return (float)(int)(__float_as_uint(a) - __float_as_uint(b));
+    return a - b;
+}
+
+// FP64 difference x_i - x_j of a near pair (i: position xi of the FP32
+// record): from the FP64 positions when given (nearest image in a box), else
+// from the FP32 records (exact difference of floats, or the fixed-point
+// difference times s).
+template <bool PER>
+__device__ __forceinline__ void near_diff_v(float xi, float yi, float zi, int i, float4 pj, int jg,
+                                            const PairConst& pc, const double* __restrict__ x64,
+                                            double& d0, double& d1, double& d2)
+{
+    if (x64) {
+        d0 = x64[3 * (size_t)i + 0] - x64[3 * (size_t)jg + 0];
+        d1 = x64[3 * (size_t)i + 1] - x64[3 * (size_t)jg + 1];
+        d2 = x64[3 * (size_t)i + 2] - x64[3 * (size_t)jg + 2];
+        if (PER) nearest_image_d(pc, d0, d1, d2);
+    } else if (PER) {
+        d0 = (double)(int)(__float_as_uint(xi) - __float_as_uint(pj.x)) * pc.s_q;
+        d1 = (double)(int)(__float_as_uint(yi) - __float_as_uint(pj.y)) * pc.s_q;
+        d2 = (double)(int)(__float_as_uint(zi) - __float_as_uint(pj.z)) * pc.s_q;
+    } else {
+        d0 = (double)xi - (double)pj.x;
+        d1 = (double)yi - (double)pj.y;
+        d2 = (double)zi - (double)pj.z;
+    }
+}
+
 // v += rows s = 0, 1, ..., S-1 of a split-row array (component c of particle
 // i of row s at partial[(3 s + c) n + i]), added in that order.  The loads of
 // ROWS_IN_FLIGHT rows are issued before the first of their adds, so a thread
@@ -79,6 +113,27 @@ __device__ __forceinline__ void add_split_rows(const double* __restrict__ partia
             }
         }
     }
+}
+
+// Fixed-point coordinate of a periodic box (q = x 2^32 / Lb mod 2^32, see
+// PairConst), returned as the bits of a float record.  qs = 2^32 / Lb.
+__device__ __forceinline__ float fixed_coord(double x, double qs)
+{
+    const long long t = (long long)rint(x * qs);
+    return __uint_as_float((unsigned int)(unsigned long long)t);
+}
+
+// FP32 record of a position: plain FP32 (qs = 0) or fixed point (qs > 0).
+__device__ __forceinline__ void put_pos(float4* p, int i, double a, double b, double c, double qs)
+{
+    if (qs > 0.0)
+        p[i] = make_float4(fixed_coord(a, qs), fixed_coord(b, qs), fixed_coord(c, qs), 0.0f);
+    else
+        p[i] = make_float4((float)a, (float)b, (float)c, 0.0f);
+}
+__device__ __forceinline__ void put_pos(double4* p, int i, double a, double b, double c, double)
+{
+    p[i] = make_double4(a, b, c, 0.0);
 }
 
 }  // namespace sd

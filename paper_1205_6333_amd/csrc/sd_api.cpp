@@ -385,7 +385,10 @@ sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* f
     hipEvent_t ev;
     prof_begin(st, &ev);
     hipError_t e;
-    if (L.variant == 3)
+    if (L.variant == 3 && prec != SD_FP64)
+        e = launch_wave_f32(L, p->tensor, L.acc != 0, (const float4*)pos, (const float4*)frc, x64,
+                            (int)n, pc, partial, st);
+    else if (L.variant == 3)
         e = launch_wave_f64(L, p->tensor, (const double4*)pos, (const double4*)frc, (int)n, pc,
                             partial, st);
     else if (prec == SD_FP64)
@@ -396,8 +399,8 @@ sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* f
                             (int)n, pc, partial, st);
     prof_end(st, ev);
     if (e == hipSuccess && L.variant == 3 && vel)
-        e = launch_wave_fold_f64(L, (int)n, pc, partial, (const double4*)frc, vel, nullptr,
-                                 nullptr, nullptr, 0.0, 0, nullptr, st);
+        e = launch_wave_fold(L, prec == SD_FP64, (int)n, pc, partial, frc, vel, nullptr, nullptr,
+                             nullptr, 0.0, 0, nullptr, st);
     const bool fuse = vel && (L.variant == 2 || L.variant == 3);
     if (e == hipSuccess && prec != SD_FP64)
         e = launch_pair_fold(L, p->tensor, (const float4*)pos, (const float4*)frc, x64, (int)n, pc,
@@ -415,8 +418,8 @@ sd_status finish_step(const sd_params* p, int64_t n, const void* frc, int32_t pr
     const double mu0 = 1.0 / (6.0 * M_PI * p->eta * p->a);
     hipError_t e;
     if (L.variant == 3)
-        e = launch_wave_fold_f64(L, (int)n, pair_const(p), partial, (const double4*)frc, nullptr,
-                                 x, v_prev, v_out, dt, mode, (double4*)pos_next, st);
+        e = launch_wave_fold(L, prec == SD_FP64, (int)n, pair_const(p), partial, frc, nullptr, x,
+                             v_prev, v_out, dt, mode, pos_next, st);
     else if (prec == SD_FP64)
         e = launch_merge_integrate_f64(partial, L.splits, (int)n, (const double4*)frc, mu0, x,
                                        v_prev, v_out, dt, mode, (double4*)pos_next, st);
@@ -435,9 +438,9 @@ PairLaunch plan_wave(int64_t n, int ilp)
     L.block = 256;
     L.ilp = ilp;
     L.cus = device_cus();
-    // two rounds of four waves per SIMD (one and four rounds time alike at
-    // N = 8192 and 16384: the chunks are small, and more rounds mean more
-    // split rows for the fold to read)
+    // two rounds of four waves per SIMD (one round and four time within a few
+    // percent of it at N = 8192 and 16384; so does dealing the chunks evenly
+    // to a whole number of rounds)
     L.jchunk = 32 * L.cus;
     L.splits = wave_shape_of(L, (int)n).splits + 1;
     return L;
@@ -450,6 +453,12 @@ PairLaunch plan_pair(int32_t prec, int64_t n)
     if (automatic && prec == SD_FP64 && n >= WAVE_F64_MIN_N) {
         const PairLaunch W = plan_wave(n, n >= WAVE_ILP2_MIN_N ? 2 : 1);
         if (partial_bytes(W, n) <= SYM_WORKSPACE_CAP) return W;
+    }
+    if (automatic && prec != SD_FP64 && n >= WAVE_F32_MIN_N &&
+        n < (prec == SD_FP32_KAHAN ? SYM_MIN_N : WAVE_PLAIN_END_N)) {
+        PairLaunch W = plan_wave(n, n >= WAVE_F32_ILP2_MIN_N ? 2 : 1);
+        W.acc = prec == SD_FP32_KAHAN ? 1 : 0;
+        return W;
     }
     PairLaunch L = shape_pair_launch((int)n, c.variant, c.block, c.splits, c.ilp, device_cus());
     L.acc = (prec == SD_FP64) ? 0 : c.kahan_block;

@@ -59,6 +59,19 @@ bool sym_fits(int64_t n, int block);
 // 16384 301 / 246 / 200, 40000 1730 / - / 1107.
 constexpr int64_t WAVE_F64_MIN_N = 1024;
 constexpr int64_t WAVE_ILP2_MIN_N = 3500;
+// Automatic FP32 products: wave-symmetric from WAVE_F32_MIN_N to where the
+// block-symmetric kernel (fewer j-side partials, more pairs per tile) is as
+// fast, two particles per lane (with SD_FP32_KAHAN in assembly) from
+// WAVE_F32_ILP2_MIN_N on.  Microseconds per mobility_apply, before / one / two
+// particles per lane: N = 1024 15.5 / 13.2 / -, 2000 17.0 / 13.1 / -, 3000 21.2
+// / 14.8 / -, 4096 24.5 / 19.6 / 21.0, 6007 43.9 / 30.9 / 28.5, 8192 54.4 /
+// 47.2 / 42.8, 12000 107.7 / - / 77.5; block-symmetric and wave at 16384 124.2
+// and 126.8 (162.5 and 132.8 with one particle in ten overlapping), 24576 243
+// and 301.  Plain sums (compiled loops in both): 16384 149 and 126, 24576 277
+// and 286.
+constexpr int64_t WAVE_F32_MIN_N = 1024;
+constexpr int64_t WAVE_F32_ILP2_MIN_N = 5000;
+constexpr int64_t WAVE_PLAIN_END_N = 20000;
 // The configuration for n particles; *automatic (may be null) receives whether
 // it is the automatic choice (nothing forced, no tuned shape for the size).
 sd_kernel_config choose_config(int32_t prec, int64_t n, bool* automatic = nullptr);

@@ -138,15 +138,19 @@ hipError_t launch_pair_fold(const PairLaunch& L, int tensor, const float4* pos, 
                             const double* x64, int n, const PairConst& pc, double* partial,
                             hipStream_t st, double mu0 = 0.0, double* vel = nullptr);
 
-// Variant 3 (wave_sym.h): the FP64 pair kernel, and the fold that adds its
-// partials and writes velocities (vel given) or does the time step (vel null;
-// arguments as launch_merge_integrate_f64).
+// Variant 3 (wave_sym.h): the pair kernels (x64 as for launch_pair_f32, kahan:
+// compensated i-side sums), and the fold that adds their partials and writes
+// velocities (vel given) or does the time step (vel null; the other arguments
+// as launch_merge_integrate_*).
 hipError_t launch_wave_f64(const PairLaunch& L, int tensor, const double4* pos, const double4* frc,
                            int n, const PairConst& pc, double* partial, hipStream_t st);
-hipError_t launch_wave_fold_f64(const PairLaunch& L, int n, const PairConst& pc,
-                                const double* partial, const double4* frc, double* vel, double* x,
-                                double* v_prev, double* v_out, double dt, int mode,
-                                double4* pos_next, hipStream_t st);
+hipError_t launch_wave_f32(const PairLaunch& L, int tensor, bool kahan, const float4* pos,
+                           const float4* frc, const double* x64, int n, const PairConst& pc,
+                           double* partial, hipStream_t st);
+hipError_t launch_wave_fold(const PairLaunch& L, bool f64, int n, const PairConst& pc,
+                            const double* partial, const void* frc, double* vel, double* x,
+                            double* v_prev, double* v_out, double dt, int mode, void* pos_next,
+                            hipStream_t st);
 
 // v_i = mu0 F_i + sum_s partial_s (fixed order).
 // Read the current device's counts of pairs with 0 < r < 2a and r = 0 met by

@@ -80,35 +80,6 @@ __device__ __forceinline__ AdjCoef<double> adj_near_coef(const PairConst& pc, do
     return c;
 }
 
-template <typename T>
-struct V3 {
-    T x, y, z;
-};
-template <typename T>
-__device__ __forceinline__ T dot(const V3<T>& a, const V3<T>& b)
-{
-    return fma(a.x, b.x, fma(a.y, b.y, a.z * b.z));
-}
-
-template <typename T>
-__device__ __forceinline__ V3<T> add(const V3<T>& a, const V3<T>& b)
-{
-    return { a.x + b.x, a.y + b.y, a.z + b.z };
-}
-template <typename T>
-__device__ __forceinline__ void keep(V3<T>& v)
-{
-    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z));
-}
-// s += y with the rounding error kept: y started from the last -error c
-template <typename T>
-__device__ __forceinline__ void kahan(V3<T>& s, V3<T>& c, const V3<T>& y)
-{
-    const V3<T> t = add(s, y);
-    c = { y.x - (t.x - s.x), y.y - (t.y - s.y), y.z - (t.z - s.z) };
-    s = t;
-}
-
 // One pair: G to g and cg, T lam_j to m, T lam_i to cm (the terms of j; first:
 // cg and cm are started; start: g and m are started).
 template <typename T>
@@ -184,14 +155,7 @@ k_wave_adjoint(const typename Vec4<T>::type* __restrict__ pos,
         ib = u - s * sh.nb;
     }
     int pbeg, pend;
-    if (diag) {
-        pbeg = w * 16 * ILP;
-        pend = pbeg + 16 * ILP;
-    } else {
-        const int lI = (sh.h + ((sh.extra && ib < (sh.nb >> 1)) ? 1 : 0)) * B;
-        pbeg = (s * 4 + w) * 16 * sh.chunks;
-        pend = min(lI, pbeg + 16 * sh.chunks);
-    }
+    wave_range<B>(sh, diag, ib, s, w, pbeg, pend);
     const T far = (T)1.0e15;
     const V3<T> zero = { (T)0, (T)0, (T)0 };
     V3<T> x[ILP], f[ILP], l[ILP], g[ILP], m[ILP];

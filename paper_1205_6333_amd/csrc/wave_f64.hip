@@ -1,6 +1,5 @@
 // wave_f64.hip -- the FP64 product v = M(x) F with each pair of particles
-// evaluated once (wave-symmetric schedule, wave_sym.h), and the fold that
-// turns its partial sums into velocities or into the next positions.
+// evaluated once (wave-symmetric schedule, wave_sym.h).
 #include "pair_terms.h"
 #include "premise.h"
 #include "sd_internal.h"
@@ -21,47 +20,6 @@ __device__ __forceinline__ uint32_t high_word(double v)
     return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32);
 }
 
-// Far coefficients A', Bt' of a pair (scaled units, see PairConst).
-template <int TENSOR>
-__device__ __forceinline__ void far_coef(double rinv, double gamma, double m3g, double& A,
-                                         double& Bt)
-{
-    const double rinv2 = rinv * rinv, rinv3 = rinv2 * rinv;
-    if (TENSOR == T_OSEEN) {
-        A = rinv;
-        Bt = rinv3;
-    } else {
-        A = fma(gamma, rinv3, rinv);
-        Bt = rinv3 * fma(m3g, rinv2, 1.0);
-    }
-}
-
-// Coefficients of a near pair (r^2 below the threshold), in the same scaled
-// units, from the definitions of near_term; returns its premise class.
-template <int TENSOR>
-__device__ __forceinline__ int near_coef(const PairConst& pc, double r2, double& A, double& Bt)
-{
-    const double ialpha = 1.0 / pc.alpha;
-    if (r2 == 0.0) {
-        A = (TENSOR == T_RPY && pc.overlap) ? pc.mu0 * ialpha : 0.0;
-        Bt = 0.0;
-        return PREMISE_COINCIDENT;
-    }
-    const double r = sqrt(r2);
-    if (TENSOR == T_OSEEN) {
-        A = 1.0 / r;
-        Bt = A / r2;
-    } else if (pc.overlap && r < 2.0 * pc.a) {
-        A = pc.mu0 * ialpha * (1.0 - 9.0 * r / (32.0 * pc.a));
-        Bt = pc.mu0 * ialpha * 3.0 / (32.0 * pc.a * r);
-    } else {
-        const double ri = 1.0 / r, ri2 = ri * ri, ri3 = ri * ri2;
-        A = ri + pc.gamma * ri3;
-        Bt = ri3 * (1.0 - 3.0 * pc.gamma * ri2);
-    }
-    return r2 < 4.0 * pc.a * pc.a ? PREMISE_SUB2A : PREMISE_OK;
-}
-
 // One pair: T F_j to the sums of i, T F_i to the term c for j (first: c is
 // started).
 __device__ __forceinline__ void pair_sums(WaveI64& L, double A, double Bt, double dx, double dy,
@@ -78,8 +36,8 @@ __device__ __forceinline__ void pair_sums(WaveI64& L, double A, double Bt, doubl
     c2 = fma(A, L.fz, first ? si * dz : fma(si, dz, c2));
 }
 
-// partial: FP64 split rows (isplits, then the diagonal row), physical units;
-// jpart[c][I][p]: FP64 j-side partials, scaled units.
+// partial: FP64 split rows (isplits, then the diagonal row); jpart[c][I][p]:
+// FP64 j-side partials.
 //
 // Bound by the FP64 vector ALU: about 36 operations of four cycles, one
 // v_rsq_f64 and, per two pairs, the hand-over of three sums (six moves, three
@@ -111,16 +69,8 @@ k_wave_f64(const double4* __restrict__ pos, const double4* __restrict__ frc, int
         s = u / sh.nb;
         ib = u - s * sh.nb;
     }
-    // this wave's positions: of the virtual range, or of the block itself
     int pbeg, pend;
-    if (diag) {
-        pbeg = w * 16 * ILP;
-        pend = pbeg + 16 * ILP;
-    } else {
-        const int lI = (sh.h + ((sh.extra && ib < (sh.nb >> 1)) ? 1 : 0)) * B;
-        pbeg = (s * 4 + w) * 16 * sh.chunks;
-        pend = min(lI, pbeg + 16 * sh.chunks);
-    }
+    wave_range<B>(sh, diag, ib, s, w, pbeg, pend);
     WaveI64 L[ILP];
 #pragma unroll
     for (int l = 0; l < ILP; ++l) {
@@ -255,7 +205,8 @@ k_wave_f64(const double4* __restrict__ pos, const double4* __restrict__ frc, int
             wave_lds_fence();
             if (lane < 48) {
                 const double sum = ((sj[lane] + sj[48 + lane]) + sj[96 + lane]) + sj[144 + lane];
-                jpart[((size_t)row * sh.nb + ib) * (size_t)sh.lmax + (size_t)(p + q)] = sum;
+                jpart[((size_t)row * sh.nb + ib) * (size_t)sh.lmax + (size_t)(p + q)] =
+                    pc.alpha * sum;
             }
         }
     }
@@ -272,94 +223,6 @@ k_wave_f64(const double4* __restrict__ pos, const double4* __restrict__ frc, int
             partial[((size_t)s * 3 + c) * (size_t)n + i] =
                 pc.alpha * (((s_i[0][t] + s_i[1][t]) + s_i[2][t]) + s_i[3][t]);
     }
-}
-
-// Sum of the partials of a particle: its j-side partials of the blocks
-// I = J - 1, J - 2, ... (and the antipode), times alpha, and its split rows.
-// A work-group takes 32 particles; its eight slices of 32 lanes take every
-// eighth term, each with its loads issued in groups, and the slices are added
-// in order.  Then, by mode: velocities (mu0 F + sum), or a step of the time
-// loop (as k_merge_integrate); the positions may be updated in place, since
-// the pair kernel has finished with them.
-__global__ void __launch_bounds__(256)
-k_wave_fold_f64(const double* __restrict__ partial, const double* __restrict__ jpart, int n, int B,
-                WaveShape sh, double alpha, const double4* __restrict__ frc, double mu0,
-                double* __restrict__ vel, double* __restrict__ x, double* __restrict__ v_prev,
-                double* __restrict__ v_out, double dt, int mode, double4* __restrict__ pos_next)
-{
-    __shared__ double s_sum[8][3][32];
-    const int t = threadIdx.x & 31, sl = threadIdx.x >> 5;
-    const int i = blockIdx.x * 32 + t;
-    double v[3] = { 0.0, 0.0, 0.0 };
-    if (i < n) {
-        const int J = i / B, o = i - J * B;
-        const int half = sh.nb >> 1;
-        const size_t cs = (size_t)sh.nb * (size_t)sh.lmax;
-        const int Ie = J >= half ? J - half : J + half;
-        const int nd = sh.h + ((sh.extra && Ie < half) ? 1 : 0);
-        double a[3] = { 0.0, 0.0, 0.0 };
-        constexpr int G = 4;
-        for (int d0 = sl; d0 < nd; d0 += 8 * G) {
-            double g[G][3];
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const int d = d0 + 8 * u;   // block I = J - d - 1 (mod nb)
-                if (d < nd) {
-                    int I = J - d - 1;
-                    if (I < 0) I += sh.nb;
-                    const double* at = jpart + (size_t)I * sh.lmax + (size_t)d * B + o;
-                    g[u][0] = at[0];
-                    g[u][1] = at[cs];
-                    g[u][2] = at[2 * cs];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < G; ++u)
-                if (d0 + 8 * u < nd)
-                    for (int c = 0; c < 3; ++c) a[c] += g[u][c];
-        }
-        const int rows = sh.splits + 1;
-        const size_t rs = 3 * (size_t)n;
-        for (int r0 = sl; r0 < rows; r0 += 8 * G) {
-            double g[G][3];
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const int r = r0 + 8 * u;
-                if (r < rows) {
-                    const double* at = partial + (size_t)r * rs + i;
-                    g[u][0] = at[0];
-                    g[u][1] = at[n];
-                    g[u][2] = at[2 * (size_t)n];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < G; ++u)
-                if (r0 + 8 * u < rows)
-                    for (int c = 0; c < 3; ++c) v[c] += g[u][c];
-        }
-        for (int c = 0; c < 3; ++c) v[c] = fma(alpha, a[c], v[c]);
-    }
-    for (int c = 0; c < 3; ++c) s_sum[sl][c][t] = v[c];
-    __syncthreads();
-    if (sl != 0 || i >= n) return;
-    const double4 f = frc[i];
-    double u[3] = { mu0 * f.x, mu0 * f.y, mu0 * f.z };
-    for (int k = 0; k < 8; ++k)
-        for (int c = 0; c < 3; ++c) u[c] += s_sum[k][c][t];
-    if (vel) {
-        for (int c = 0; c < 3; ++c) vel[3 * (size_t)i + c] = u[c];
-        return;
-    }
-    double xn[3];
-    for (int c = 0; c < 3; ++c) {
-        const size_t e = 3 * (size_t)i + c;
-        const double inc = (mode == 2) ? (1.5 * u[c] - 0.5 * v_prev[e]) : u[c];
-        xn[c] = x[e] + dt * inc;
-        x[e] = xn[c];
-        if (mode != 0) v_prev[e] = u[c];
-        if (v_out) v_out[e] = u[c];
-    }
-    if (pos_next) pos_next[i] = make_double4(xn[0], xn[1], xn[2], 0.0);
 }
 
 hipError_t launch_wave_f64(const PairLaunch& L, int tensor, const double4* pos, const double4* frc,
@@ -385,19 +248,6 @@ hipError_t launch_wave_f64(const PairLaunch& L, int tensor, const double4* pos, 
     }
 #undef SD_ILP
 #undef SD_GO
-    return hipGetLastError();
-}
-
-hipError_t launch_wave_fold_f64(const PairLaunch& L, int n, const PairConst& pc,
-                                const double* partial, const double4* frc, double* vel, double* x,
-                                double* v_prev, double* v_out, double dt, int mode,
-                                double4* pos_next, hipStream_t st)
-{
-    const WaveShape sh = wave_shape_of(L, n);
-    const double* jpart = (const double*)((const char*)partial + wave_jpart_offset(sh, n));
-    hipLaunchKernelGGL(k_wave_fold_f64, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, partial,
-                       jpart, n, 64 * L.ilp, sh, pc.alpha, frc, pc.mu0, vel, x, v_prev, v_out, dt,
-                       mode, pos_next);
     return hipGetLastError();
 }
 

@@ -7,7 +7,7 @@
 // i-block I takes the blocks I + 1 .. I + h (mod nb), h = (nb - 1) / 2, and,
 // when nb is even, block I + nb/2 if I < nb/2: a virtual j range in which
 // every unordered pair of distinct blocks appears once.  A work-group of four
-// waves owns one i-block and one split of its range, 4 x 16 chunks positions;
+// waves owns one i-block and one split of its range;
 // all four waves hold the same particles i and each walks its own chunks of
 // 16 particles j.  The diagonal blocks are taken one-sided by nb extra
 // work-groups, their chunks dealt to the four waves.
@@ -25,6 +25,7 @@
 // the split rows stay as few as the work-groups' ranges.
 #pragma once
 
+#include "pair_terms.h"
 #include "sd_internal.h"
 
 #include <type_traits>
@@ -46,15 +47,30 @@ inline WaveShape wave_shape(int n, int B, int waves)
     s.extra = (s.nb >= 2 && (s.nb & 1) == 0) ? 1 : 0;
     s.lmax = (s.h + s.extra) * B;
     const int64_t total = (int64_t)s.nb * (s.lmax / 16);
-    int64_t c = (total + waves - 1) / waves;
+    const int64_t c = (total + waves - 1) / waves;
     s.chunks = (int)(c < 1 ? 1 : c);
     s.splits = (s.lmax + 64 * s.chunks - 1) / (64 * s.chunks);
     return s;
 }
-
 inline WaveShape wave_shape_of(const PairLaunch& L, int n)
 {
     return wave_shape(n, 64 * L.ilp, L.jchunk);
+}
+
+// Positions [pbeg, pend) of wave w of split s: of the virtual range of i-block
+// ib, or (diag) of the block itself.
+template <int B>
+__device__ __forceinline__ void wave_range(const WaveShape& sh, bool diag, int ib, int s, int w,
+                                           int& pbeg, int& pend)
+{
+    if (diag) {
+        pbeg = w * (B / 4);
+        pend = pbeg + B / 4;
+    } else {
+        const int lI = (sh.h + ((sh.extra && ib < (sh.nb >> 1)) ? 1 : 0)) * B;
+        pbeg = (s * 4 + w) * 16 * sh.chunks;
+        pend = min(lI, pbeg + 16 * sh.chunks);
+    }
 }
 
 // Workspace: the split rows and the diagonal row (f64[3n] each), then
@@ -110,6 +126,76 @@ __device__ __forceinline__ double rsqrt_f64(double x)
     const double t = x * y;
     const double h = fma(-t, y, 1.0);
     return fma(y * h, fma(h, 0.375, 0.5), y);
+}
+
+// Far coefficients A', Bt' of a pair (scaled units, see PairConst).
+template <int TENSOR>
+__device__ __forceinline__ void far_coef(double rinv, double gamma, double m3g, double& A,
+                                         double& Bt)
+{
+    const double rinv2 = rinv * rinv, rinv3 = rinv2 * rinv;
+    if (TENSOR == T_OSEEN) {
+        A = rinv;
+        Bt = rinv3;
+    } else {
+        A = fma(gamma, rinv3, rinv);
+        Bt = rinv3 * fma(m3g, rinv2, 1.0);
+    }
+}
+
+// Coefficients of a near pair (r^2 below the threshold), scaled by 1 / alpha,
+// from the definitions of near_term; returns its premise class.
+template <int TENSOR>
+__device__ __forceinline__ int near_coef(const PairConst& pc, double r2, double& A, double& Bt)
+{
+    const double ialpha = 1.0 / pc.alpha;
+    if (r2 == 0.0) {
+        A = (TENSOR == T_RPY && pc.overlap) ? pc.mu0 * ialpha : 0.0;
+        Bt = 0.0;
+        return PREMISE_COINCIDENT;
+    }
+    const double r = sqrt(r2);
+    if (TENSOR == T_OSEEN) {
+        A = 1.0 / r;
+        Bt = A / r2;
+    } else if (pc.overlap && r < 2.0 * pc.a) {
+        A = pc.mu0 * ialpha * (1.0 - 9.0 * r / (32.0 * pc.a));
+        Bt = pc.mu0 * ialpha * 3.0 / (32.0 * pc.a * r);
+    } else {
+        const double ri = 1.0 / r, ri2 = ri * ri, ri3 = ri * ri2;
+        A = ri + pc.gamma * ri3;
+        Bt = ri3 * (1.0 - 3.0 * pc.gamma * ri2);
+    }
+    return r2 < 4.0 * pc.a * pc.a ? PREMISE_SUB2A : PREMISE_OK;
+}
+
+template <typename T>
+struct V3 {
+    T x, y, z;
+};
+template <typename T>
+__device__ __forceinline__ T dot(const V3<T>& a, const V3<T>& b)
+{
+    return fma(a.x, b.x, fma(a.y, b.y, a.z * b.z));
+}
+
+template <typename T>
+__device__ __forceinline__ V3<T> add(const V3<T>& a, const V3<T>& b)
+{
+    return { a.x + b.x, a.y + b.y, a.z + b.z };
+}
+template <typename T>
+__device__ __forceinline__ void keep(V3<T>& v)
+{
+    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z));
+}
+// s += y with the rounding error kept: y started from the last -error c
+template <typename T>
+__device__ __forceinline__ void kahan(V3<T>& s, V3<T>& c, const V3<T>& y)
+{
+    const V3<T> t = add(s, y);
+    c = { y.x - (t.x - s.x), y.y - (t.y - s.y), y.z - (t.z - s.z) };
+    s = t;
 }
 
 // Orders a wave's LDS accesses across its lanes (one wave, in-order LDS: no

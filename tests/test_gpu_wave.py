@@ -56,18 +56,47 @@ def test_f64_product(sd, orc, n, form):
     assert counts == tuple(orc.premise_counts(po, x))
 
 
-@pytest.mark.parametrize("integ", [0, 1])
-def test_f64_time_steps(sd, orc, integ):
-    """The fold that also takes the time step: three steps against the oracle."""
-    n, dt = 1100, 0.01
-    x, _ = _positions(n, False, False)
-    f = W.gravity_forces(n) + 0.2 * W.gaussian_forces(n, seed=5)
+@pytest.mark.parametrize("n", [1024, 1025, 1088, 4999, 5000, 5120, 5121, 5249])
+@pytest.mark.parametrize("prec", [0, 2])
+@pytest.mark.parametrize("form", ["rpy", "overlap", "oseen", "box"])
+def test_f32_product(sd, orc, n, prec, form):
+    """The same for the FP32 products (tolerances of the one-sided kernels'
+    tests: 1e-6 compensated, 1e-5 plain)."""
     import torch
+    x, L = _positions(n, form == "box", form != "oseen")
+    x, f = W.round_to_f32(x), W.round_to_f32(W.gaussian_forces(n, seed=n + 1))
+    kw = dict(overlap=form != "rpy", tensor=1 if form == "oseen" else 0,
+              box=L if form == "box" else None)
+    sd.sd_premise_counts(reset=True)
+    v = sd.mobility_apply(to_dev4(x, torch.float32), to_dev4(f, torch.float32),
+                          params=sd.params(**kw), precision=prec)
+    counts = sd.sd_premise_counts(reset=True)
+    po = orc.params(**kw)
+    ref = orc.mobility(po, x, f)
+    tol = 1e-6 if prec == 0 else 1e-5
+    assert rel2(v.cpu().numpy(), ref) <= tol and rowerr(v.cpu().numpy(), ref) <= 10 * tol
+    assert counts == tuple(orc.premise_counts(po, x))
+
+
+@pytest.mark.parametrize("n,prec,tol", [(1100, 1, 1e-12), (1100, 0, 1e-6), (5200, 0, 1e-6)])
+@pytest.mark.parametrize("integ", [0, 1])
+@pytest.mark.parametrize("box", [False, True])
+@pytest.mark.parametrize("steps", [3, 40])
+def test_time_steps(sd, orc, n, prec, tol, integ, box, steps):
+    """The fold that also takes the time step, eager (3 steps) and with graph
+    replays (40), against the oracle: displacements within tol."""
+    import torch
+    if steps == 40 and n > 2000:
+        pytest.skip("the oracle's 40 steps of the larger size take too long")
+    x, L = _positions(n, box, False)
+    f, dt = W.gravity_forces(n) + 0.2 * W.gaussian_forces(n, seed=5), 0.002
+    if prec != 1:
+        f = W.round_to_f32(f)
     xd, vp = to_dev3(x), to_dev3(np.zeros_like(x))
-    sd.sd_run(xd, to_dev4(f, torch.float64), dt, 3, v_prev=vp, integrator=integ,
-              precision=sd.SD_FP64)
-    ref = orc.run(orc.params(), x, f, dt, 3, integrator=integ)[0]
-    assert np.abs(xd.cpu().numpy() - ref).max() <= 1e-12 * np.abs(ref - x).max() + 1e-13
+    sd.sd_run(xd, to_dev4(f, torch.float64 if prec == 1 else torch.float32), dt, steps, v_prev=vp,
+              integrator=integ, precision=prec, params=sd.params(box=L if box else None))
+    ref = orc.run(orc.params(box=L if box else None), x, f, dt, steps, integrator=integ)[0]
+    assert rel2(xd.cpu().numpy() - x, ref - x) <= tol
 
 
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 193, 1000])
