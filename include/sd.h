@@ -82,7 +82,8 @@ typedef enum sd_precision {
                              over the i-block, rounded to FP32 once per i-block
                              and j and added in FP64 */
     SD_FP64 = 1,          /* FP64 throughout */
-    SD_FP32_PLAIN = 2     /* FP32 evaluation and plain FP32 accumulation */
+    SD_FP32_PLAIN = 2     /* FP32 evaluation and plain FP32 accumulation (the
+                             automatic choice may sum more accurately) */
 } sd_precision;
 
 typedef enum sd_integrator {
@@ -427,7 +428,12 @@ typedef struct sd_kernel_config {
                              bytes.  The automatic choice takes it from
                              n = 16384 on (block 256, ilp 2, kahan_block
                              32 for SD_FP32_KAHAN) while that workspace
-                             stays within 1 GiB */
+                             stays within 1 GiB.  Where the automatic choice
+                             names variant 0 (and for SD_FP32_PLAIN below n =
+                             20000) it runs kernels of its own instead, with
+                             no shape to choose: small products as whole rows
+                             in one launch, larger ones with each pair
+                             evaluated once */
     int32_t block;        /* work-group size (64, 128 or 256; variant 2: 128,
                              256 or 512) */
     int32_t splits;       /* j-range splits (>= 1): extra work-groups per i-block */
@@ -442,7 +448,9 @@ typedef struct sd_kernel_config {
 
 /* Force a configuration for a precision (NULL restores automatic choice). */
 sd_status sd_set_kernel_config(int32_t precision, const sd_kernel_config* cfg);
-/* The configuration mobility_apply would use for n particles. */
+/* The configuration mobility_apply would use for n particles (the automatic
+ * choice's own kernels are not configurations, see variant; forcing what is
+ * returned here runs the general kernel of that shape). */
 sd_status sd_get_kernel_config(int32_t precision, int64_t n, sd_kernel_config* out);
 
 /*

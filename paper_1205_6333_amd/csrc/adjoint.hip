@@ -611,45 +611,46 @@ sd_status sd_run_adjoint(const sd_params* p, int64_t n, const double* x0, const 
         }
         ck = xw;
     }
-    void *traj = nullptr, *pos = nullptr, *lam4 = nullptr;
+    void *traj = nullptr, *recs = nullptr, *lam4 = nullptr;
+    const PairLaunch L = plan_pair(precision, n);
+    StepBuffers sb;
     if ((st = ws_get(WS_ADJ_TRAJ, frame * (size_t)E, &traj)) ||
-        (st = ws_get(WS_STAGE, rec * (size_t)n, &pos)) ||
+        (st = ws_get(WS_ADJ_REC, rec * (size_t)n * (size_t)E, &recs)) ||
+        (st = step_buffers(L, n, precision, &sb)) ||
         (st = ws_get(WS_ADJ_PACK, rec * (size_t)n, &lam4)))
         return st;
     // lam lives in grad_x0 (initialised with grad_xN above)
     double* lam = grad_x0;
     double* T = (double*)traj;
+    char* R = (char*)recs;
     const int64_t nseg = (steps + E - 1) / E;
     bool have_lam4 = false;
     for (int64_t seg = nseg - 1; seg >= 0; --seg) {
         const int64_t k0 = seg * E;
         const int64_t k1 = std::min(steps, k0 + E);
-        // x_{k0} .. x_{k1-1}: recompute the segment from its checkpoint with the
-        // forward kernels (bitwise the forward pass's states)
-        if (hipMemcpyAsync(T, ck + m * (size_t)seg, frame, hipMemcpyDeviceToDevice, hs) !=
-            hipSuccess)
-            return fail(SD_EDEVICE, "copy failed");
-        for (int64_t k = k0; k + 1 < k1; ++k) {
-            double* nxt = T + m * (size_t)(k - k0 + 1);
-            if (hipMemcpyAsync(nxt, T + m * (size_t)(k - k0), frame, hipMemcpyDeviceToDevice, hs) !=
-                hipSuccess)
-                return fail(SD_EDEVICE, "copy failed");
-            if ((st = sd_step(p, n, nxt, force, nullptr, nullptr, dt, k, SD_EULER, precision,
-                              stream)))
+        // x_{k0} .. x_{k1-1} and their records: recompute the segment from its
+        // checkpoint with the forward kernels (bitwise the forward pass's
+        // states), each step into the next frame
+        const double* x0k = ck + m * (size_t)seg;
+        auto state = [&](int64_t k) { return k == k0 ? x0k : T + m * (size_t)(k - k0); };
+        auto record = [&](int64_t k) { return R + rec * (size_t)n * (size_t)(k - k0); };
+        hipError_t e = launch_stage(f64, x0k, record(k0), (int)n, 0.0, nullptr, hs);
+        if (e != hipSuccess) return fail(SD_EDEVICE, "stage launch: %s", hipGetErrorString(e));
+        for (int64_t k = k0; k + 1 < k1; ++k)
+            if ((st = run_step(p, n, state(k), T + m * (size_t)(k + 1 - k0), force, nullptr,
+                               nullptr, dt, 0, precision, record(k), record(k + 1), sb.partial, L,
+                               hs)))
                 return st;
-        }
         for (int64_t k = k1 - 1; k >= k0; --k) {
-            const double* xk = T + m * (size_t)(k - k0);
-            hipError_t e;
-            e = f64 ? launch_pack_f64(xk, (double4*)pos, (int)n, hs)
-                    : launch_pack_f32(xk, (float4*)pos, (int)n, hs);
-            if (e == hipSuccess && !have_lam4)
+            if (!have_lam4) {
                 e = f64 ? launch_pack_f64(lam, (double4*)lam4, (int)n, hs)
                         : launch_pack_f32(lam, (float4*)lam4, (int)n, hs);
-            if (e != hipSuccess) return fail(SD_EDEVICE, "pack launch: %s", hipGetErrorString(e));
+                if (e != hipSuccess)
+                    return fail(SD_EDEVICE, "pack launch: %s", hipGetErrorString(e));
+            }
             // dL/dF += dt M(x_k) lam_{k+1};  lam_k = lam_{k+1} + dt d/dx [lam_{k+1} . M(x_k) F]
-            if ((st = adjoint_pass(p, n, pos, force, lam4, f64 ? nullptr : xk, precision, lam, dt,
-                                   nullptr, grad_force, hs, &have_lam4)))
+            if ((st = adjoint_pass(p, n, record(k), force, lam4, f64 ? nullptr : state(k),
+                                   precision, lam, dt, nullptr, grad_force, hs, &have_lam4)))
                 return st;
         }
     }

@@ -8,11 +8,14 @@ namespace sd {
 
 template <typename P4>
 __global__ void __launch_bounds__(256) k_stage(const double* __restrict__ x, P4* __restrict__ pos,
-                                               int n, double qs)
+                                               int n, double qs, double* __restrict__ copy)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    put_pos(pos, i, x[3 * (size_t)i], x[3 * (size_t)i + 1], x[3 * (size_t)i + 2], qs);
+    const double v[3] = { x[3 * (size_t)i], x[3 * (size_t)i + 1], x[3 * (size_t)i + 2] };
+    put_pos(pos, i, v[0], v[1], v[2], qs);
+    if (copy)
+        for (int k = 0; k < 3; ++k) copy[3 * (size_t)i + k] = v[k];
 }
 
 __global__ void __launch_bounds__(256) k_stage_q_from_f32(const float4* __restrict__ pos,
@@ -25,14 +28,15 @@ __global__ void __launch_bounds__(256) k_stage_q_from_f32(const float4* __restri
 }
 
 // v_k = mu0 F + sum_s partial_s (the same order as k_merge), then
-//   mode 0: x += dt v                       (Euler)
-//   mode 1: x += dt v,  v_prev = v           (first AB2 step)
-//   mode 2: x += dt (3/2 v - 1/2 v_prev), v_prev = v   (AB2)
+//   mode 0: x_out = x_in + dt v                       (Euler)
+//   mode 1: x_out = x_in + dt v,  v_prev = v           (first AB2 step)
+//   mode 2: x_out = x_in + dt (3/2 v - 1/2 v_prev), v_prev = v   (AB2)
+// (x_out may be x_in)
 // and the staged copy of the new positions for the next pair kernel.
 template <typename F4, typename P4>
 __global__ void __launch_bounds__(256)
 k_merge_integrate(const double* __restrict__ partial, int S, int n, const F4* __restrict__ frc,
-                  double mu0, double* __restrict__ x, double* __restrict__ v_prev,
+                  double mu0, const double* x_in, double* x_out, double* __restrict__ v_prev,
                   double* __restrict__ v_out, double dt, int mode, P4* __restrict__ pos_next,
                   double qs)
 {
@@ -46,8 +50,8 @@ k_merge_integrate(const double* __restrict__ partial, int S, int n, const F4* __
     for (int k = 0; k < 3; ++k) {
         const size_t e = 3 * (size_t)i + k;
         const double inc = (mode == 2) ? (1.5 * v[k] - 0.5 * v_prev[e]) : v[k];
-        xn[k] = x[e] + dt * inc;
-        x[e] = xn[k];
+        xn[k] = x_in[e] + dt * inc;
+        x_out[e] = xn[k];
         if (mode != 0) v_prev[e] = v[k];
         if (v_out) v_out[e] = v[k];
     }
@@ -171,16 +175,15 @@ static inline dim3 grid_for(int64_t n) { return dim3((unsigned)((n + 255) / 256)
 // 2^32 / Lb, the fixed-point scale of a periodic box (0 in free space)
 static inline double q_scale(double box) { return box > 0.0 ? 4294967296.0 / box : 0.0; }
 
-hipError_t launch_stage_f32(const double* x, float4* pos, int n, double box, hipStream_t st)
+hipError_t launch_stage(bool f64, const double* x, void* pos, int n, double box, double* copy,
+                        hipStream_t st)
 {
-    hipLaunchKernelGGL((k_stage<float4>), grid_for(n), dim3(256), 0, st, x, pos, n,
-                       q_scale(box));
-    return hipGetLastError();
-}
-
-hipError_t launch_stage_f64(const double* x, double4* pos, int n, hipStream_t st)
-{
-    hipLaunchKernelGGL((k_stage<double4>), grid_for(n), dim3(256), 0, st, x, pos, n, 0.0);
+    if (f64)
+        hipLaunchKernelGGL((k_stage<double4>), grid_for(n), dim3(256), 0, st, x, (double4*)pos, n,
+                           0.0, copy);
+    else
+        hipLaunchKernelGGL((k_stage<float4>), grid_for(n), dim3(256), 0, st, x, (float4*)pos, n,
+                           q_scale(box), copy);
     return hipGetLastError();
 }
 
@@ -192,22 +195,19 @@ hipError_t launch_stage_q_from_f32(const float4* pos, float4* q, int n, double b
     return hipGetLastError();
 }
 
-hipError_t launch_merge_integrate_f32(const double* partial, int splits, int n, const float4* frc,
-                                      double mu0, double* x, double* v_prev, double* v_out,
-                                      double dt, int mode, float4* pos_next, double box,
-                                      hipStream_t st)
+hipError_t launch_merge_integrate(bool f64, const double* partial, int splits, int n,
+                                  const void* frc, double mu0, const double* x_in, double* x_out,
+                                  double* v_prev, double* v_out, double dt, int mode,
+                                  void* pos_next, double box, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_merge_integrate<float4, float4>), grid_for(n), dim3(256), 0, st, partial,
-                       splits, n, frc, mu0, x, v_prev, v_out, dt, mode, pos_next, q_scale(box));
-    return hipGetLastError();
-}
-
-hipError_t launch_merge_integrate_f64(const double* partial, int splits, int n, const double4* frc,
-                                      double mu0, double* x, double* v_prev, double* v_out,
-                                      double dt, int mode, double4* pos_next, hipStream_t st)
-{
-    hipLaunchKernelGGL((k_merge_integrate<double4, double4>), grid_for(n), dim3(256), 0, st,
-                       partial, splits, n, frc, mu0, x, v_prev, v_out, dt, mode, pos_next, 0.0);
+    if (f64)
+        hipLaunchKernelGGL((k_merge_integrate<double4, double4>), grid_for(n), dim3(256), 0, st,
+                           partial, splits, n, (const double4*)frc, mu0, x_in, x_out, v_prev, v_out,
+                           dt, mode, (double4*)pos_next, 0.0);
+    else
+        hipLaunchKernelGGL((k_merge_integrate<float4, float4>), grid_for(n), dim3(256), 0, st,
+                           partial, splits, n, (const float4*)frc, mu0, x_in, x_out, v_prev, v_out,
+                           dt, mode, (float4*)pos_next, q_scale(box));
     return hipGetLastError();
 }
 

@@ -464,29 +464,23 @@ sd_status sd_run_lub(const sd_params* p, const sd_lub* lub, int64_t n, double* x
     const bool f64 = precision == SD_FP64;
     const size_t rec = f64 ? 32 : 16;
     const PairLaunch L = plan_pair(precision, n);
-    void *partial = nullptr, *stage = nullptr, *F4 = nullptr;
-    if ((st = ws_get(WS_PARTIAL, partial_bytes(L, n), &partial)) ||
-        (st = ws_get(WS_STAGE, rec * (size_t)n, &stage)) ||
-        (st = ws_get(WS_LUB_F, rec * (size_t)n, &F4)))
+    StepBuffers sb;
+    void* F4 = nullptr;
+    if ((st = step_buffers(L, n, precision, &sb)) || (st = ws_get(WS_LUB_F, rec * (size_t)n, &F4)))
         return st;
     // per step: forces with the correction (written straight into the force
-    // records of the pair kernel), pair kernel, then merge + integrate, which
-    // also stages the new positions for the next step
-    hipError_t e = f64 ? launch_stage_f64(x, (double4*)stage, (int)n, hs)
-                       : launch_stage_f32(x, (float4*)stage, (int)n, box_side(p), hs);
-    if (e != hipSuccess) return fail(SD_EDEVICE, "staging launch: %s", hipGetErrorString(e));
+    // records of the pair kernel), then the step, which also stages the new
+    // positions for the next one
+    if ((st = steps_begin(p, n, x, steps, precision, L, &sb, hs))) return st;
     for (int64_t s = 0; s < steps; ++s) {
         const int64_t k = step0 + s;
-        if ((st = lub_forces_impl(p, lub, n, x, v_prev, f_ext, nullptr,
+        if ((st = lub_forces_impl(p, lub, n, sb.cur, v_prev, f_ext, nullptr,
                                   f64 ? nullptr : (float4*)F4, f64 ? (double4*)F4 : nullptr, hs)))
-            return st;
-        if ((st = run_pair(p, n, stage, F4, f64 ? nullptr : x, precision, (double*)partial, L, hs)))
             return st;
         // Euler: x += dt v, v_prev = v;  AB2: x += dt (3/2 v - 1/2 v_prev), v_prev = v
         const int mode = (integrator == SD_EULER) ? 0 : (k == 0 ? 1 : 2);
-        const bool next = s + 1 < steps;
-        if ((st = finish_step(p, n, F4, precision, (double*)partial, L, x, mode ? v_prev : nullptr,
-                              mode ? nullptr : v_prev, dt, mode, next ? stage : nullptr, hs)))
+        if ((st = steps_next(p, n, F4, mode ? v_prev : nullptr, mode ? nullptr : v_prev, dt, mode,
+                             precision, L, s + 1 < steps, &sb, hs)))
             return st;
     }
     return SD_OK;

@@ -385,9 +385,17 @@ sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* f
     hipEvent_t ev;
     prof_begin(st, &ev);
     hipError_t e;
+    if (L.variant == 4) {   // (a product: the steps go through run_step)
+        e = launch_row(L, prec == SD_FP64, p->tensor, pos, frc, x64, (int)n, pc, vel, nullptr,
+                       nullptr, nullptr, nullptr, 0.0, 0, nullptr, st);
+        prof_end(st, ev);
+        if (e != hipSuccess) return fail(SD_EDEVICE, "row launch: %s", hipGetErrorString(e));
+        if (merged) *merged = true;
+        return SD_OK;
+    }
     if (L.variant == 3 && prec != SD_FP64)
-        e = launch_wave_f32(L, p->tensor, L.acc != 0, (const float4*)pos, (const float4*)frc, x64,
-                            (int)n, pc, partial, st);
+        e = launch_wave_f32(L, p->tensor, (const float4*)pos, (const float4*)frc, x64, (int)n, pc,
+                            partial, st);
     else if (L.variant == 3)
         e = launch_wave_f64(L, p->tensor, (const double4*)pos, (const double4*)frc, (int)n, pc,
                             partial, st);
@@ -400,7 +408,7 @@ sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* f
     prof_end(st, ev);
     if (e == hipSuccess && L.variant == 3 && vel)
         e = launch_wave_fold(L, prec == SD_FP64, (int)n, pc, partial, frc, vel, nullptr, nullptr,
-                             nullptr, 0.0, 0, nullptr, st);
+                             nullptr, nullptr, 0.0, 0, nullptr, st);
     const bool fuse = vel && (L.variant == 2 || L.variant == 3);
     if (e == hipSuccess && prec != SD_FP64)
         e = launch_pair_fold(L, p->tensor, (const float4*)pos, (const float4*)frc, x64, (int)n, pc,
@@ -411,24 +419,73 @@ sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* f
     return SD_OK;
 }
 
-sd_status finish_step(const sd_params* p, int64_t n, const void* frc, int32_t prec,
-                      const double* partial, const PairLaunch& L, double* x, double* v_prev,
-                      double* v_out, double dt, int mode, void* pos_next, hipStream_t st)
+sd_status run_step(const sd_params* p, int64_t n, const double* x_in, double* x_out,
+                   const void* frc, double* v_prev, double* v_out, double dt, int mode,
+                   int32_t prec, const void* pos, void* pos_next, double* partial,
+                   const PairLaunch& L, hipStream_t st)
 {
-    const double mu0 = 1.0 / (6.0 * M_PI * p->eta * p->a);
+    const bool f64 = prec == SD_FP64;
     hipError_t e;
+    if (L.variant == 4) {
+        hipEvent_t ev;
+        prof_begin(st, &ev);
+        e = launch_row(L, f64, p->tensor, pos, frc, x_in, (int)n, pair_const(p), nullptr, x_in,
+                       x_out, v_prev, v_out, dt, mode, pos_next, st);
+        prof_end(st, ev);
+        if (e != hipSuccess) return fail(SD_EDEVICE, "step launch: %s", hipGetErrorString(e));
+        return SD_OK;
+    }
+    sd_status r = run_pair(p, n, pos, frc, f64 ? nullptr : x_in, prec, partial, L, st);
+    if (r) return r;
     if (L.variant == 3)
-        e = launch_wave_fold(L, prec == SD_FP64, (int)n, pair_const(p), partial, frc, nullptr, x,
+        e = launch_wave_fold(L, f64, (int)n, pair_const(p), partial, frc, nullptr, x_in, x_out,
                              v_prev, v_out, dt, mode, pos_next, st);
-    else if (prec == SD_FP64)
-        e = launch_merge_integrate_f64(partial, L.splits, (int)n, (const double4*)frc, mu0, x,
-                                       v_prev, v_out, dt, mode, (double4*)pos_next, st);
     else
-        e = launch_merge_integrate_f32(partial, L.splits, (int)n, (const float4*)frc, mu0, x,
-                                       v_prev, v_out, dt, mode, (float4*)pos_next, box_side(p),
-                                       st);
+        e = launch_merge_integrate(f64, partial, L.splits, (int)n, frc,
+                                   1.0 / (6.0 * M_PI * p->eta * p->a), x_in, x_out, v_prev, v_out,
+                                   dt, mode, pos_next, f64 ? 0.0 : box_side(p), st);
     if (e != hipSuccess) return fail(SD_EDEVICE, "integrate launch: %s", hipGetErrorString(e));
     return SD_OK;
+}
+
+sd_status step_buffers(const PairLaunch& L, int64_t n, int32_t prec, StepBuffers* sb)
+{
+    sd_status st;
+    void *partial = nullptr, *stage = nullptr, *copy = nullptr;
+    const size_t rec = ((size_t)n * (prec == SD_FP64 ? 32 : 16) + 255) & ~(size_t)255;
+    if ((st = ws_get(WS_PARTIAL, partial_bytes(L, n), &partial)) ||
+        (st = ws_get(WS_STAGE, 2 * rec, &stage)))
+        return st;
+    if (L.variant == 4 && (st = ws_get(WS_STEP_X, 3 * (size_t)n * sizeof(double), &copy)))
+        return st;
+    sb->partial = (double*)partial;
+    sb->pos[0] = (char*)stage;
+    sb->pos[1] = L.variant == 4 ? (char*)stage + rec : (char*)stage;
+    sb->copy = (double*)copy;
+    return SD_OK;
+}
+
+sd_status steps_begin(const sd_params* p, int64_t n, double* x, int64_t steps, int32_t prec,
+                      const PairLaunch& L, StepBuffers* sb, hipStream_t st)
+{
+    const bool odd = L.variant == 4 && (steps & 1);
+    const hipError_t e = launch_stage(prec == SD_FP64, x, sb->pos[0], (int)n, box_side(p),
+                                      odd ? sb->copy : nullptr, st);
+    if (e != hipSuccess) return fail(SD_EDEVICE, "stage launch: %s", hipGetErrorString(e));
+    sb->cur = odd ? sb->copy : x;
+    sb->other = L.variant == 4 && !odd ? sb->copy : x;
+    return SD_OK;
+}
+
+sd_status steps_next(const sd_params* p, int64_t n, const void* frc, double* v_prev, double* v_out,
+                     double dt, int mode, int32_t prec, const PairLaunch& L, bool more,
+                     StepBuffers* sb, hipStream_t st)
+{
+    const sd_status r = run_step(p, n, sb->cur, sb->other, frc, v_prev, v_out, dt, mode, prec,
+                                 sb->pos[0], more ? sb->pos[1] : nullptr, sb->partial, L, st);
+    std::swap(sb->cur, sb->other);
+    std::swap(sb->pos[0], sb->pos[1]);
+    return r;
 }
 
 PairLaunch plan_wave(int64_t n, int ilp)
@@ -450,15 +507,20 @@ PairLaunch plan_pair(int32_t prec, int64_t n)
 {
     bool automatic = false;
     const sd_kernel_config c = choose_config(prec, n, &automatic);
-    if (automatic && prec == SD_FP64 && n >= WAVE_F64_MIN_N) {
-        const PairLaunch W = plan_wave(n, n >= WAVE_ILP2_MIN_N ? 2 : 1);
-        if (partial_bytes(W, n) <= SYM_WORKSPACE_CAP) return W;
-    }
-    if (automatic && prec != SD_FP64 && n >= WAVE_F32_MIN_N &&
-        n < (prec == SD_FP32_KAHAN ? SYM_MIN_N : WAVE_PLAIN_END_N)) {
-        PairLaunch W = plan_wave(n, n >= WAVE_F32_ILP2_MIN_N ? 2 : 1);
-        W.acc = prec == SD_FP32_KAHAN ? 1 : 0;
-        return W;
+    if (automatic) {
+        const bool f64 = prec == SD_FP64;
+        if (n < (f64 ? ROW_F64_END_N : ROW_F32_END_N)) {
+            PairLaunch L{};
+            L.variant = 4;
+            L.block = 256;
+            L.ilp = n >= ROW_ILP2_MIN_N ? 2 : 1;
+            L.splits = 1;
+            return L;
+        }
+        if (f64 || n < (prec == SD_FP32_KAHAN ? SYM_MIN_N : WAVE_PLAIN_END_N)) {
+            const PairLaunch W = plan_wave(n, 2);
+            if (partial_bytes(W, n) <= SYM_WORKSPACE_CAP) return W;
+        }
     }
     PairLaunch L = shape_pair_launch((int)n, c.variant, c.block, c.splits, c.ilp, device_cus());
     L.acc = (prec == SD_FP64) ? 0 : c.kahan_block;
@@ -469,6 +531,7 @@ PairLaunch plan_pair(int32_t prec, int64_t n)
 size_t partial_bytes(const PairLaunch& L, int64_t n)
 {
     if (L.variant == 2) return sym_workspace_bytes(L, n);
+    if (L.variant == 4) return 0;
     if (L.variant == 3) {
         const WaveShape sh = wave_shape_of(L, (int)n);
         return wave_jpart_offset(sh, n) + wave_jpart_bytes(sh, sizeof(double));
@@ -501,6 +564,7 @@ struct RunKey {
     sd::PairLaunch L{};
     void* partial = nullptr;
     void* stage = nullptr;
+    void* copy = nullptr;
     bool operator==(const RunKey& o) const { return std::memcmp(this, &o, sizeof(RunKey)) == 0; }
 };
 
@@ -587,26 +651,10 @@ sd_status mobility_apply(const sd_params* p, int64_t n, const void* pos, const v
     return SD_OK;
 }
 
-// One time step from x (FP64).  pos_stage holds the staged copy of x on entry
-// when `staged` is true.
-static sd_status step_impl(const sd_params* p, int64_t n, double* x, const void* force,
-                           double* v_prev, double* v_out, double dt, int64_t step_index,
-                           int32_t integrator, int32_t prec, void* pos_stage, bool staged,
-                           bool stage_next, double* partial, const PairLaunch& L, hipStream_t hs)
+// mode of launch_merge_integrate for the step with a global index
+static int step_mode(int32_t integrator, int64_t step_index)
 {
-    sd_status st;
-    hipError_t e;
-    if (!staged) {
-        e = (prec == SD_FP64) ? launch_stage_f64(x, (double4*)pos_stage, (int)n, hs)
-                              : launch_stage_f32(x, (float4*)pos_stage, (int)n, box_side(p), hs);
-        if (e != hipSuccess) return fail(SD_EDEVICE, "stage launch: %s", hipGetErrorString(e));
-    }
-    if ((st = run_pair(p, n, pos_stage, force, prec == SD_FP64 ? nullptr : x, prec, partial, L,
-                       hs)))
-        return st;
-    const int mode = (integrator == SD_EULER) ? 0 : (step_index == 0 ? 1 : 2);
-    return finish_step(p, n, force, prec, partial, L, x, v_prev, v_out, dt, mode,
-                       stage_next ? pos_stage : nullptr, hs);
+    return integrator == SD_EULER ? 0 : (step_index == 0 ? 1 : 2);
 }
 
 static sd_status check_step_args(const sd_params* p, int64_t n, const double* x, const void* force,
@@ -634,13 +682,12 @@ sd_status sd_step(const sd_params* p, int64_t n, double* x, const void* force, d
     if (v_out && (uintptr_t)v_out % 8) return fail(SD_EALIGN, "v_out is not 8-byte aligned");
     hipStream_t hs = (hipStream_t)stream;
     const PairLaunch L = plan_pair(precision, n);
-    void *partial = nullptr, *stage = nullptr;
-    if ((st = ws_get(WS_PARTIAL, partial_bytes(L, n), &partial)) ||
-        (st = ws_get(WS_STAGE, (size_t)n * (precision == SD_FP64 ? 32 : 16), &stage)))
+    StepBuffers sb;
+    if ((st = step_buffers(L, n, precision, &sb)) ||
+        (st = steps_begin(p, n, x, 1, precision, L, &sb, hs)))
         return st;
-    return step_impl(p, n, x, force, integrator == SD_AB2 ? v_prev : nullptr, v_out, dt,
-                     step_index, integrator, precision, stage, false, false, (double*)partial, L,
-                     hs);
+    return steps_next(p, n, force, integrator == SD_AB2 ? v_prev : nullptr, v_out, dt,
+                      step_mode(integrator, step_index), precision, L, false, &sb, hs);
 }
 
 sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, double* v_prev,
@@ -661,10 +708,8 @@ sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, do
         return fail(SD_EDEVICE, "checkpoint copy failed");
     if (steps == 0) return SD_OK;
     const PairLaunch L = plan_pair(precision, n);
-    void *partial = nullptr, *stage = nullptr;
-    if ((st = ws_get(WS_PARTIAL, partial_bytes(L, n), &partial)) ||
-        (st = ws_get(WS_STAGE, (size_t)n * (precision == SD_FP64 ? 32 : 16), &stage)))
-        return st;
+    StepBuffers sb;
+    if ((st = step_buffers(L, n, precision, &sb))) return st;
     double* vp = integrator == SD_AB2 ? v_prev : nullptr;
     int64_t done = 0;
     const int32_t gmode = g_graph_mode.load();
@@ -673,8 +718,8 @@ sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, do
     if (graphed) {
         // the first AB2 step (an Euler step that stores v_prev) stays eager
         if (integrator == SD_AB2 && step0 == 0) {
-            if ((st = step_impl(p, n, x, force, vp, nullptr, dt, 0, integrator, precision, stage,
-                                false, false, (double*)partial, L, hs)))
+            if ((st = steps_begin(p, n, x, 1, precision, L, &sb, hs)) ||
+                (st = steps_next(p, n, force, vp, nullptr, dt, 1, precision, L, false, &sb, hs)))
                 return st;
             done = 1;
         }
@@ -692,8 +737,11 @@ sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, do
         key.mode = integrator == SD_EULER ? 0 : 2;
         key.prec = precision;
         key.L = L;
-        key.partial = partial;
-        key.stage = stage;
+        // (the capture starts from the first record array whatever ran before)
+        if ((st = step_buffers(L, n, precision, &sb))) return st;
+        key.partial = sb.partial;
+        key.stage = sb.pos[0];
+        key.copy = sb.copy;
         std::lock_guard<std::mutex> lk(g_rg_mu);
         RunGraph& g = g_rg[dev];
         if (!g.cap && hipStreamCreateWithFlags(&g.cap, hipStreamNonBlocking) != hipSuccess)
@@ -704,10 +752,10 @@ sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, do
             drop_run_graph(g);
             if (hipStreamBeginCapture(g.cap, hipStreamCaptureModeThreadLocal) != hipSuccess)
                 return fail(SD_EDEVICE, "hipStreamBeginCapture failed");
-            sd_status cst = SD_OK;
+            sd_status cst = steps_begin(p, n, x, RUN_CHUNK, precision, L, &sb, g.cap);
             for (int k = 0; k < RUN_CHUNK && !cst; ++k)   // step index 1: never the AB2 start
-                cst = step_impl(p, n, x, force, vp, nullptr, dt, 1, integrator, precision, stage,
-                                k > 0, k + 1 < RUN_CHUNK, (double*)partial, L, g.cap);
+                cst = steps_next(p, n, force, vp, nullptr, dt, step_mode(integrator, 1), precision,
+                                 L, k + 1 < RUN_CHUNK, &sb, g.cap);
             hipGraph_t graph = nullptr;
             const hipError_t e2 = hipStreamEndCapture(g.cap, &graph);
             if (cst || e2 != hipSuccess || !graph) {
@@ -728,13 +776,14 @@ sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, do
                 return fail(SD_EDEVICE, "hipGraphLaunch failed");
         if (hipEventRecord(g.done, hs) != hipSuccess) return fail(SD_EDEVICE, "event record failed");
     }
+    if (done < steps && (st = steps_begin(p, n, x, steps - done, precision, L, &sb, hs))) return st;
     for (int64_t s = done; s < steps; ++s) {
-        if ((st = step_impl(p, n, x, force, vp, nullptr, dt, step0 + s, integrator, precision, stage,
-                            s > done, s + 1 < steps, (double*)partial, L, hs)))
+        if ((st = steps_next(p, n, force, vp, nullptr, dt, step_mode(integrator, step0 + s),
+                             precision, L, s + 1 < steps, &sb, hs)))
             return st;
         if (x_checkpoints && (s + 1) % checkpoint_every == 0) {
             double* dst = x_checkpoints + 3 * (size_t)n * (size_t)((s + 1) / checkpoint_every);
-            if (hipMemcpyAsync(dst, x, frame, hipMemcpyDeviceToDevice, hs) != hipSuccess)
+            if (hipMemcpyAsync(dst, sb.cur, frame, hipMemcpyDeviceToDevice, hs) != hipSuccess)
                 return fail(SD_EDEVICE, "checkpoint copy failed");
         }
     }

@@ -13,9 +13,11 @@ constexpr int64_t MAX_N = (int64_t(1) << 30);
 // Library-owned workspace slots (one buffer each per device).
 enum {
     WS_PARTIAL = 0,   // split partials of the pair kernels
-    WS_STAGE,         // FP32 / FP64 staged positions of the time loop
+    WS_STAGE,         // FP32 / FP64 staged positions of the time loop (two copies)
+    WS_STEP_X,        // positions of every other step (variant 4)
     WS_ADJ_PARTIAL,   // split partials of the adjoint kernel
-    WS_ADJ_PACK,      // packed cotangent / force staging
+    WS_ADJ_PACK,      // packed cotangent
+    WS_ADJ_REC,       // position records of one checkpoint segment
     WS_ADJ_TRAJ,      // recomputed trajectory of one checkpoint segment
     WS_ADJ_LAM,       // adjoint state
     WS_ADJ_CKPT,      // checkpoints when the caller passes none
@@ -49,28 +51,24 @@ constexpr size_t SYM_WORKSPACE_CAP = (size_t)1 << 30;
 // Smallest n for which the automatic configuration takes variant 2.
 constexpr int64_t SYM_MIN_N = 16384;
 bool sym_fits(int64_t n, int block);
-// Automatic FP64 products of at least WAVE_F64_MIN_N particles take the
-// wave-symmetric kernel (variant 3) while its workspace stays within the cap,
-// with two particles per lane from WAVE_ILP2_MIN_N on (one per lane gives
-// twice the waves of a small product; two share each hand-over and each read
-// of j).  Microseconds per mobility_apply, one-sided kernel / one / two
-// particles per lane: N = 1024 16.9 / 14.3 / 16.4, 2000 18.9 / 14.2 / -,
-// 3001 27.6 / 18.2 / 20.0, 4000 34.5 / 25.6 / 24.5, 6000 72.6 / 46.0 / 39.7,
-// 16384 301 / 246 / 200, 40000 1730 / - / 1107.
-constexpr int64_t WAVE_F64_MIN_N = 1024;
-constexpr int64_t WAVE_ILP2_MIN_N = 3500;
-// Automatic FP32 products: wave-symmetric from WAVE_F32_MIN_N to where the
-// block-symmetric kernel (fewer j-side partials, more pairs per tile) is as
-// fast, two particles per lane (with SD_FP32_KAHAN in assembly) from
-// WAVE_F32_ILP2_MIN_N on.  Microseconds per mobility_apply, before / one / two
-// particles per lane: N = 1024 15.5 / 13.2 / -, 2000 17.0 / 13.1 / -, 3000 21.2
-// / 14.8 / -, 4096 24.5 / 19.6 / 21.0, 6007 43.9 / 30.9 / 28.5, 8192 54.4 /
-// 47.2 / 42.8, 12000 107.7 / - / 77.5; block-symmetric and wave at 16384 124.2
-// and 126.8 (162.5 and 132.8 with one particle in ten overlapping), 24576 243
-// and 301.  Plain sums (compiled loops in both): 16384 149 and 126, 24576 277
-// and 286.
-constexpr int64_t WAVE_F32_MIN_N = 1024;
-constexpr int64_t WAVE_F32_ILP2_MIN_N = 5000;
+// What the automatic choice runs beyond the configurations of sd.h.
+//
+// Rows in one launch (variant 4) below ROW_*_END_N, two particles per
+// work-group from ROW_ILP2_MIN_N on.  Above, each pair once: the wave-symmetric
+// kernel (variant 3) for FP64 wherever its workspace fits, for FP32 up to where
+// the block-symmetric kernel (variant 2: fewer j-side partials, more pairs per
+// tile) is as fast.  Microseconds per Euler step, FP32, rows with two
+// particles / wave-symmetric: N = 4500 19.9 / 22.2, 5324 25.3 / 26.9, 6007 30.5
+// / 29.6; FP64: N = 3500 18.8 / 22.5, 4000 23.8 / 23.6, 5000 34.3 / 30.4.
+// Microseconds per product, wave- / block-symmetric (compensated): N = 12000
+// 77.5 / -, 16384 126.8 / 124.2 (with one particle in ten overlapping 132.8 /
+// 162.5), 24576 301 / 243; plain sums (the block-symmetric loop is compiled
+// there) 16384 126 / 149, 20000 188 / 198, 24576 301 / 277.  FP64,
+// wave-symmetric / one-sided: N = 6000 39.7 / 72.6, 16384 199 / 301, 40000 1107
+// / 1730.
+constexpr int64_t ROW_F32_END_N = 5900;
+constexpr int64_t ROW_F64_END_N = 4000;
+constexpr int64_t ROW_ILP2_MIN_N = 1300;
 constexpr int64_t WAVE_PLAIN_END_N = 20000;
 // The configuration for n particles; *automatic (may be null) receives whether
 // it is the automatic choice (nothing forced, no tuned shape for the size).
@@ -84,18 +82,37 @@ PairLaunch plan_pair(int32_t prec, int64_t n);
 // a wave-symmetric launch (variant 3) with ilp particles per lane
 PairLaunch plan_wave(int64_t n, int ilp);
 size_t partial_bytes(const PairLaunch& L, int64_t n);
-// vel (may be null): for the pair-symmetric kernel the product is finished
-// here (the fold merges into vel; *merged is set), else the caller merges.
+// vel (may be null): for variants 2 to 4 the product is finished here (*merged
+// is set), else the caller merges.
 sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* frc,
                    const double* x64, int32_t prec, double* partial, const PairLaunch& L,
                    hipStream_t st, double* vel = nullptr, bool* merged = nullptr);
 
-// One time step's end: split rows -> v, positions and history (mode as
-// launch_merge_integrate_*), and the staged copy for the next pair kernel.
-// Enqueue after run_pair (without vel).
-sd_status finish_step(const sd_params* p, int64_t n, const void* frc, int32_t prec,
-                      const double* partial, const PairLaunch& L, double* x, double* v_prev,
-                      double* v_out, double dt, int mode, void* pos_next, hipStream_t st);
+// One time step from x_in to x_out (mode as launch_merge_integrate).  pos: the
+// records of x_in; pos_next (may be null) receives those of x_out.  x_out may
+// be x_in and pos_next may be pos unless the launch is of variant 4.
+sd_status run_step(const sd_params* p, int64_t n, const double* x_in, double* x_out,
+                   const void* frc, double* v_prev, double* v_out, double dt, int mode,
+                   int32_t prec, const void* pos, void* pos_next, double* partial,
+                   const PairLaunch& L, hipStream_t st);
+
+// A sequence of steps that starts and ends in the caller's x.  Variants 0 to 3
+// work in place; variant 4 alternates between x and a library copy (and between
+// two record arrays), beginning with the copy when the number of steps is odd.
+struct StepBuffers {
+    double* partial = nullptr;
+    char* pos[2] = { nullptr, nullptr };   // records: of the current positions first
+    double* copy = nullptr;                // variant 4
+    double* cur = nullptr;                 // the current positions
+    double* other = nullptr;               // where the next step puts them
+};
+sd_status step_buffers(const PairLaunch& L, int64_t n, int32_t prec, StepBuffers* sb);
+sd_status steps_begin(const sd_params* p, int64_t n, double* x, int64_t steps, int32_t prec,
+                      const PairLaunch& L, StepBuffers* sb, hipStream_t st);
+// more: another step follows (its records are staged)
+sd_status steps_next(const sd_params* p, int64_t n, const void* frc, double* v_prev, double* v_out,
+                     double dt, int mode, int32_t prec, const PairLaunch& L, bool more,
+                     StepBuffers* sb, hipStream_t st);
 
 void batch_release_graphs();
 void run_graphs_release();

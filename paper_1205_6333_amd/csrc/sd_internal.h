@@ -66,7 +66,7 @@ PairConst make_pair_const(double a, double eta, int tensor, int overlap, double 
 
 struct PairLaunch {
     int variant;   // 0 LDS tiles, 1 scalar-cache j stream, 2 pair symmetry (FP32 only),
-                   // 3 wave-symmetric (automatic choice only)
+                   // automatic choice only: 3 wave-symmetric, 4 rows in one launch
     int block;     // threads per work-group
     int splits;    // number of partial rows written (variants 0/1: j-range splits)
     int jchunk;    // variants 0/1: particles j per split (multiple of block);
@@ -138,19 +138,28 @@ hipError_t launch_pair_fold(const PairLaunch& L, int tensor, const float4* pos, 
                             const double* x64, int n, const PairConst& pc, double* partial,
                             hipStream_t st, double mu0 = 0.0, double* vel = nullptr);
 
-// Variant 3 (wave_sym.h): the pair kernels (x64 as for launch_pair_f32, kahan:
-// compensated i-side sums), and the fold that adds their partials and writes
+// Variant 3 (wave_sym.h): the pair kernels (x64 as for launch_pair_f32; both
+// with two particles per lane), and the fold that adds their partials and writes
 // velocities (vel given) or does the time step (vel null; the other arguments
-// as launch_merge_integrate_*).
+// as launch_merge_integrate).
 hipError_t launch_wave_f64(const PairLaunch& L, int tensor, const double4* pos, const double4* frc,
                            int n, const PairConst& pc, double* partial, hipStream_t st);
-hipError_t launch_wave_f32(const PairLaunch& L, int tensor, bool kahan, const float4* pos,
-                           const float4* frc, const double* x64, int n, const PairConst& pc,
-                           double* partial, hipStream_t st);
+hipError_t launch_wave_f32(const PairLaunch& L, int tensor, const float4* pos, const float4* frc,
+                           const double* x64, int n, const PairConst& pc, double* partial,
+                           hipStream_t st);
 hipError_t launch_wave_fold(const PairLaunch& L, bool f64, int n, const PairConst& pc,
-                            const double* partial, const void* frc, double* vel, double* x,
-                            double* v_prev, double* v_out, double dt, int mode, void* pos_next,
-                            hipStream_t st);
+                            const double* partial, const void* frc, double* vel,
+                            const double* x_in, double* x_out, double* v_prev, double* v_out,
+                            double dt, int mode, void* pos_next, hipStream_t st);
+
+// Variant 4 (row_product.hip): the whole product (vel given) or time step in
+// one launch.  x64, x_in: positions before the step, of which other
+// work-groups read the particles near theirs: x_out is another array, and
+// pos_next (may be null) other records than pos.
+hipError_t launch_row(const PairLaunch& L, bool f64, int tensor, const void* pos, const void* frc,
+                      const double* x64, int n, const PairConst& pc, double* vel,
+                      const double* x_in, double* x_out, double* v_prev, double* v_out, double dt,
+                      int mode, void* pos_next, hipStream_t st);
 
 // v_i = mu0 F_i + sum_s partial_s (fixed order).
 // Read the current device's counts of pairs with 0 < r < 2a and r = 0 met by
@@ -161,21 +170,19 @@ hipError_t launch_merge_f32(const double* partial, int splits, int n, const floa
 hipError_t launch_merge_f64(const double* partial, int splits, int n, const double4* frc,
                             double mu0, double* vel, hipStream_t st);
 
-// Time loop helpers.  box > 0: the FP32 stage is the fixed-point form of a
-// periodic box of that side (see PairConst); the FP64 stage is unchanged.
-hipError_t launch_stage_f32(const double* x, float4* pos, int n, double box, hipStream_t st);
-hipError_t launch_stage_f64(const double* x, double4* pos, int n, hipStream_t st);
+// Time loop helpers.  f64: FP64 records; else FP32, and with box > 0 the
+// fixed-point form of a periodic box of that side (see PairConst).  copy (may
+// be null): a copy of x.
+hipError_t launch_stage(bool f64, const double* x, void* pos, int n, double box, double* copy,
+                        hipStream_t st);
 // fixed-point form of FP32 position records (mobility product in a box)
 hipError_t launch_stage_q_from_f32(const float4* pos, float4* q, int n, double box,
                                    hipStream_t st);
-// mode: 0 Euler, 1 AB2 start (Euler + store v_prev), 2 AB2
-hipError_t launch_merge_integrate_f32(const double* partial, int splits, int n, const float4* frc,
-                                      double mu0, double* x, double* v_prev, double* v_out,
-                                      double dt, int mode, float4* pos_next, double box,
-                                      hipStream_t st);
-hipError_t launch_merge_integrate_f64(const double* partial, int splits, int n, const double4* frc,
-                                      double mu0, double* x, double* v_prev, double* v_out,
-                                      double dt, int mode, double4* pos_next, hipStream_t st);
+// mode: 0 Euler, 1 AB2 start (Euler + store v_prev), 2 AB2; x_out may be x_in
+hipError_t launch_merge_integrate(bool f64, const double* partial, int splits, int n,
+                                  const void* frc, double mu0, const double* x_in, double* x_out,
+                                  double* v_prev, double* v_out, double dt, int mode,
+                                  void* pos_next, double box, hipStream_t st);
 
 // Adjoint pair kernels: partial[(s*3+k)*n + i] = position gradient terms,
 // partial_f[...] = pair part of (M lam)_i.

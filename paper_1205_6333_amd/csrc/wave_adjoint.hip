@@ -124,7 +124,7 @@ __device__ __forceinline__ void adj_pair(const AdjCoef<T>& c, const V3<T>& d, co
 // faster in FP32 at N = 8192 and 7 % slower there at N = 3001.  Microseconds
 // per pass with the fold (one-sided kernel and merge): FP64 N = 3001 29 (134),
 // FP32 N = 8192 86 (131).
-template <int TENSOR, typename T, int ILP>
+template <int TENSOR, typename T>
 __global__ void __launch_bounds__(256, 3)
 k_wave_adjoint(const typename Vec4<T>::type* __restrict__ pos,
                const typename Vec4<T>::type* __restrict__ frc,
@@ -134,7 +134,7 @@ k_wave_adjoint(const typename Vec4<T>::type* __restrict__ pos,
 {
     typedef typename Vec4<T>::type V4;
     constexpr bool F32 = sizeof(T) == 4;
-    constexpr int B = 64 * ILP;
+    constexpr int ILP = 1, B = 64 * ILP;
     constexpr int IB = 2, IK = 4, JB = 4;   // FP32 summation blocks
     constexpr int JH = F32 ? 2 : 1;         // j-side sums per chunk, row and element
     constexpr int RS = F32 ? 12 : 10;   // values per staged record (16-byte multiples)
@@ -520,7 +520,7 @@ size_t wave_adjoint_bytes(const PairLaunch& L, int64_t n)
     return 2 * (wave_jpart_offset(sh, n) + wave_jpart_bytes(sh, sizeof(double)));
 }
 
-template <int TENSOR, typename T, int ILP>
+template <int TENSOR, typename T>
 static hipError_t launch_t(const PairLaunch& L, const void* pos, const void* frc, void* lam,
                            const double* x64, int n, const PairConst& pc, void* ws, double* lam64,
                            double dt, double* gpos, double* gforce, hipStream_t st)
@@ -529,11 +529,11 @@ static hipError_t launch_t(const PairLaunch& L, const void* pos, const void* frc
     const WaveShape sh = wave_shape_of(L, n);
     double* partial = (double*)ws;
     double* jpart = (double*)((char*)ws + 2 * wave_jpart_offset(sh, n));
-    hipLaunchKernelGGL((k_wave_adjoint<TENSOR, T, ILP>), dim3((unsigned)(sh.nb * (sh.splits + 1))),
+    hipLaunchKernelGGL((k_wave_adjoint<TENSOR, T>), dim3((unsigned)(sh.nb * (sh.splits + 1))),
                        dim3(256), 0, st, (const V4*)pos, (const V4*)frc, (const V4*)lam, x64, n, sh,
                        pc, partial, jpart);
     hipLaunchKernelGGL((k_wave_adjoint_fold<V4>), dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st,
-                       partial, jpart, n, 64 * ILP, sh, pc.alpha, (V4*)lam, lam64, pc.mu0, dt, gpos,
+                       partial, jpart, n, 64, sh, pc.alpha, (V4*)lam, lam64, pc.mu0, dt, gpos,
                        gforce);
     return hipGetLastError();
 }
@@ -543,13 +543,13 @@ hipError_t launch_wave_adjoint(const PairLaunch& L, int tensor, bool f64, const 
                                const PairConst& pc, void* ws, double* lam64, double dt,
                                double* gpos, double* gforce, hipStream_t st)
 {
-#define SD_GO(T, I)                                                                             \
-    return tensor == T_OSEEN ? launch_t<T_OSEEN, T, I>(L, pos, frc, lam, x64, n, pc, ws, lam64, \
-                                                       dt, gpos, gforce, st)                    \
-                             : launch_t<T_RPY, T, I>(L, pos, frc, lam, x64, n, pc, ws, lam64,   \
-                                                     dt, gpos, gforce, st)
-    if (f64) SD_GO(double, 1);
-    SD_GO(float, 1);
+#define SD_GO(T)                                                                                \
+    return tensor == T_OSEEN ? launch_t<T_OSEEN, T>(L, pos, frc, lam, x64, n, pc, ws, lam64, dt, \
+                                                    gpos, gforce, st)                           \
+                             : launch_t<T_RPY, T>(L, pos, frc, lam, x64, n, pc, ws, lam64, dt,  \
+                                                  gpos, gforce, st)
+    if (f64) SD_GO(double);
+    SD_GO(float);
 #undef SD_GO
 }
 

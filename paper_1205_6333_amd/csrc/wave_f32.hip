@@ -16,9 +16,9 @@ namespace sd {
 // its registers would otherwise be the kernel's): for every step k and lane
 // particle a, test(k, a, i, jg) says whether the lane's pair is near; get(k, pj,
 // fj) reads the staged element (q + k) mod 16.  The i side goes to the lane's
-// FP64 slots own_w (component c of particle a at (c ILP + a) 64 + lane), the j
+// FP64 slots own_w (component c of particle a at (2 c + a) 64 + lane), the j
 // side of element q, summed over the rows of the wave, to nj.
-template <int TENSOR, bool PER, int ILP, class Test, class Get>
+template <int TENSOR, bool PER, class Test, class Get>
 __device__ __forceinline__ void near_chunk(const float4* __restrict__ pos,
                                            const float4* __restrict__ frc,
                                            const double* __restrict__ x64, int n, int ib, bool diag,
@@ -26,7 +26,7 @@ __device__ __forceinline__ void near_chunk(const float4* __restrict__ pos,
                                            unsigned long long* premise, V3<double>& nj, Test test,
                                            Get get)
 {
-    constexpr int B = 64 * ILP;
+    constexpr int ILP = 2, B = 64 * ILP;
     const int lane = threadIdx.x & 63, q = lane & 15;
 #pragma unroll 1
     for (int b = 0; b < 16 * ILP; ++b) {
@@ -104,207 +104,32 @@ __device__ __forceinline__ void store_sums(const double* si, int n, int ib, int 
 // partial: FP64 split rows (the diagonal row last); jpart[c][I][p]: FP64 j-side
 // partials; both in physical units.
 //
-// Sums.  i side (KAHAN): blocks of IB terms, added in FP32 and compensated once
-// per IK terms; plain otherwise.  j side: the ILP terms of a step, blocks of
-// JB steps, two of those added in FP32, and in FP64 from there on.  Near pairs
-// (r^2 below the threshold) contribute nothing in FP32: a bit per step and
-// particle sends them to the rare loop after the chunk, which evaluates them
-// in FP64 on both sides.
-template <int TENSOR, bool KAHAN, bool PER, int ILP, int IK>
-__global__ void __launch_bounds__(256, 4)
-k_wave_f32(const float4* __restrict__ pos, const float4* __restrict__ frc,
-           const double* __restrict__ x64, int n, WaveShape sh, PairConst pc,
-           double* __restrict__ partial, double* __restrict__ jpart,
-           unsigned long long* __restrict__ premise)
-{
-    constexpr int B = 64 * ILP;
-    constexpr int IB = 2, JB = 4;
-    __shared__ float4 s_pos[4][32];
-    __shared__ float4 s_frc[4][32];
-    __shared__ float s_j[4][8 * 48];
-    __shared__ double s_i[4][3 * B];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, q = lane & 15, row = lane >> 4;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool diag = (int)blockIdx.x < sh.nb;
-    int ib, s;
-    if (diag) {
-        ib = (int)blockIdx.x;
-        s = sh.splits;
-    } else {
-        const int u = (int)blockIdx.x - sh.nb;
-        s = u / sh.nb;
-        ib = u - s * sh.nb;
-    }
-    int pbeg, pend;
-    wave_range<B>(sh, diag, ib, s, w, pbeg, pend);
-    const V3<float> zero = { 0.0f, 0.0f, 0.0f };
-    V3<float> x[ILP], f[ILP], g[ILP];
-    V3<float> sum[ILP], comp[ILP], y[ILP];   // sums, -compensations, terms since the last add
-#pragma unroll
-    for (int a = 0; a < ILP; ++a) {
-        const int i = ib * B + a * 64 + lane;
-        const float far = PER ? 0.0f : SD_FAR_I;
-        x[a] = { far, far, far };
-        f[a] = g[a] = sum[a] = comp[a] = y[a] = zero;
-        if (i < n) {
-            const float4 p = pos[i], v = frc[i];
-            x[a] = { p.x, p.y, p.z };
-            f[a] = { v.x, v.y, v.z };
-        }
-#pragma unroll
-        for (int c = 0; c < 3; ++c) s_i[w][c * B + a * 64 + lane] = 0.0;   // near pairs first
-    }
-    // constants in VGPRs (an FP32 instruction with an SGPR operand issues at
-    // half rate)
-    float gamma = pc.gamma_f, m3g = pc.m3gamma_f, thr2 = pc.thr2_f, one = 1.0f;
-    asm volatile("" : "+v"(gamma), "+v"(m3g), "+v"(thr2), "+v"(one));
-    auto chunk_start = [&](int p) {
-        return diag ? ib * B + p : ((ib + 1 + p / B) % sh.nb) * B + p % B;
-    };
-    // row 0 loads the positions of a chunk, row 1 the forces
-    const float4* const src = row == 0 ? pos : frc;
-    const float fill = (row == 0 && !PER) ? SD_FAR_J : 0.0f;
-    auto load = [&](int p) {
-        const int j = chunk_start(p) + q;
-        float4 r = make_float4(fill, fill, fill, 0.0f);
-        if (row < 2 && j < n) r = src[j];
-        return r;
-    };
-    float4* const put = (row == 0 ? s_pos[w] : s_frc[w]) + q;
-    const float4* const vp = s_pos[w] + q;
-    const float4* const vf = s_frc[w] + q;
-    float4 nxt = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    if (pbeg < pend) nxt = load(pbeg);
-#pragma unroll 1
-    for (int p = pbeg; p < pend; p += 16) {
-        wave_lds_fence();
-        if (row < 2) put[0] = put[16] = nxt;
-        wave_lds_fence();
-        if (p + 16 < pend) nxt = load(p + 16);
-        V3<float> aj = zero, bj = zero;
-        uint32_t nearm = 0;   // bit k ILP + a: the pair of step k and particle a is near
-        // two steps at a time (U), their near tests taken together
-        constexpr int U = 2;
-        WaveFor<0, 16 / U>::run([&](auto g_c) {
-            constexpr int k0 = decltype(g_c)::value * U;
-            __builtin_amdgcn_sched_barrier(0);   // one group's pair data live at a time
-            V3<float> d[ILP][U], fj[U];
-            float r2[ILP][U], rmin = 0.0f;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const float4 pj = vp[k0 + u], pf = vf[k0 + u];
-                fj[u] = { pf.x, pf.y, pf.z };
-#pragma unroll
-                for (int a = 0; a < ILP; ++a) {
-                    d[a][u] = { pdiff<PER>(x[a].x, pj.x), pdiff<PER>(x[a].y, pj.y),
-                                pdiff<PER>(x[a].z, pj.z) };
-                    r2[a][u] = dot(d[a][u], d[a][u]);
-                    rmin = (a == 0 && u == 0) ? r2[a][u] : fminf(rmin, r2[a][u]);
-                }
-            }
-            if (__builtin_amdgcn_ballot_w64(rmin < thr2) != 0) {   // rare
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-#pragma unroll
-                    for (int a = 0; a < ILP; ++a) {
-                        const bool nr = r2[a][u] < thr2;
-                        nearm |= nr ? 1u << ((k0 + u) * ILP + a) : 0u;
-                        r2[a][u] = nr ? __builtin_inff() : r2[a][u];
-                    }
-            }
-            WaveFor<0, U>::run([&](auto u_c) {
-                constexpr int u = decltype(u_c)::value, k = k0 + u;
-                V3<float> c = zero;
-#pragma unroll
-                for (int a = 0; a < ILP; ++a) {
-                    const float rinv = __builtin_amdgcn_rsqf(r2[a][u]);
-                    const float rinv2 = rinv * rinv, rinv3 = rinv2 * rinv;
-                    float A = rinv, Bt = rinv3;
-                    if (TENSOR == T_RPY) {
-                        A = fmaf(gamma, rinv3, rinv);
-                        Bt = rinv3 * fmaf(m3g, rinv2, one);
-                    }
-                    const V3<float>& D = d[a][u];
-                    const float sj = Bt * dot(D, fj[u]), si = Bt * dot(D, f[a]);
-                    constexpr bool start = KAHAN && k % IB == 0;
-                    V3<float>& t = KAHAN ? g[a] : sum[a];
-                    t.x = fmaf(A, fj[u].x, start ? sj * D.x : fmaf(sj, D.x, t.x));
-                    t.y = fmaf(A, fj[u].y, start ? sj * D.y : fmaf(sj, D.y, t.y));
-                    t.z = fmaf(A, fj[u].z, start ? sj * D.z : fmaf(sj, D.z, t.z));
-                    c.x = fmaf(A, f[a].x, a == 0 ? si * D.x : fmaf(si, D.x, c.x));
-                    c.y = fmaf(A, f[a].y, a == 0 ? si * D.y : fmaf(si, D.y, c.y));
-                    c.z = fmaf(A, f[a].z, a == 0 ? si * D.z : fmaf(si, D.z, c.z));
-                    if constexpr (KAHAN && k % IB == IB - 1) {
-                        y[a] = add(k % IK == IB - 1 ? comp[a] : y[a], g[a]);
-                        if constexpr (k % IK == IK - 1) kahan(sum[a], comp[a], y[a]);
-                    }
-                }
-                if constexpr (k % JB == 0)
-                    bj = { row_rot<k>(c.x), row_rot<k>(c.y), row_rot<k>(c.z) };
-                else
-                    bj = { bj.x + row_rot<k>(c.x), bj.y + row_rot<k>(c.y), bj.z + row_rot<k>(c.z) };
-                if constexpr (k % (2 * JB) == JB - 1)
-                    aj = bj;
-                else if constexpr (k % (2 * JB) == 2 * JB - 1) {
-                    aj = add(aj, bj);
-                    float* const sr = s_j[w] + ((k / 8) * 4 + row) * 48 + q;
-                    sr[0] = aj.x;
-                    sr[16] = aj.y;
-                    sr[32] = aj.z;
-                }
-            });
-            // the sums are materialised here, or their chains sink to the end
-            // of the chunk with the terms of every step live
-            keep(aj);
-            keep(bj);
-#pragma unroll
-            for (int a = 0; a < ILP; ++a) {
-                keep(sum[a]);
-                if (KAHAN) {
-                    keep(g[a]);
-                    keep(comp[a]);
-                    keep(y[a]);
-                }
-            }
-        });
-        V3<double> nj = { 0.0, 0.0, 0.0 };   // near pairs, j side of element q
-        const bool near = __builtin_amdgcn_ballot_w64(nearm != 0) != 0;
-        if (near)   // rare
-            near_chunk<TENSOR, PER, ILP>(
-                pos, frc, x64, n, ib, diag, chunk_start(p), pc, &s_i[w][0], premise, nj,
-                [&](int k, int a, int, int) { return (nearm >> (k * ILP + a)) & 1u; },
-                [&](int k, float4& pj, float4& fj) {
-                    pj = vp[k];
-                    fj = vf[k];
-                });
-        if (!diag) store_rows(s_j[w], pc.alpha_sum, near, nj, jpart, sh, ib, p);
-    }
-#pragma unroll
-    for (int a = 0; a < ILP; ++a) {
-        double* const own = &s_i[w][a * 64 + lane];
-        own[0] += pc.alpha_sum * ((double)sum[a].x + (double)comp[a].x);
-        own[B] += pc.alpha_sum * ((double)sum[a].y + (double)comp[a].y);
-        own[2 * B] += pc.alpha_sum * ((double)sum[a].z + (double)comp[a].z);
-    }
-    __syncthreads();
-    store_sums<B>(&s_i[0][0], n, ib, s, partial);
-}
-
-// The chunk loop above with two particles per lane and the compensated i side
-// in assembly (wave_chunk_asm.h, generated by gen_sym_chunk.py): blocks of
-// four terms, compensated once per chunk of 16.  The chunk is staged as six
-// doubled float arrays (x, y, z of positions and forces), so that every
-// component is read into a register of the parity that the generated code
-// expects.
+// Two particles per lane; the chunk loop is assembly (wave_chunk_asm.h,
+// generated by gen_sym_chunk.py) with registers chosen for the VGPR read
+// ports.  The chunk is staged as six doubled float arrays (x, y, z of positions
+// and forces), so that every component is read into a register of the parity
+// that the generated code expects.
+//
+// Sums.  i side: blocks of four terms, added in FP32 and compensated once per
+// chunk of 16.  j side: the two terms of a step, blocks of four steps, two of
+// those added in FP32, and in FP64 from there on.  (Longer blocks let each term
+// be rounded into a larger partial sum: the error at N = 6007 is 0.6e-7, the
+// one-sided kernel's with blocks of eight 0.65e-7, that of the block-symmetric
+// kernel's 32 1.1e-7.)  Near pairs contribute nothing in FP32: the lanes that
+// met one send the chunk to the rare loop, which evaluates them in FP64 on both
+// sides.
+//
+// Bound by the vector ALU: 1321 instructions for the 32 pairs (64 interactions)
+// of a lane and chunk.  Microseconds per product with the fold, compiled loop /
+// assembly: N = 6007 31.7 / 28.5, 8192 47.8 / 42.8 (one-sided kernel 43.9, 54.4).
 template <int TENSOR, bool PER>
 __global__ void __launch_bounds__(256, 4)
-k_wave_f32_asm(const float4* __restrict__ pos, const float4* __restrict__ frc,
+k_wave_f32(const float4* __restrict__ pos, const float4* __restrict__ frc,
                const double* __restrict__ x64, int n, WaveShape sh, PairConst pc,
                double* __restrict__ partial, double* __restrict__ jpart,
                unsigned long long* __restrict__ premise)
 {
-    constexpr int ILP = 2, B = 64 * ILP;
+    constexpr int B = 128;
     typedef __attribute__((address_space(3))) float lds_float;
     constexpr int NC = 4, CS = 6 * 32;   // chunks staged at once, floats of one
     __shared__ float s_soa[4][NC * CS];
@@ -433,7 +258,7 @@ k_wave_f32_asm(const float4* __restrict__ pos, const float4* __restrict__ frc,
                 nearm |= dot(D1, D1) < k_thr2 ? 2u << (2 * k) : 0u;
             }
             auto test = [&](int k, int a, int, int) { return (nearm >> (2 * k + a)) & 1u; };
-            near_chunk<TENSOR, PER, ILP>(pos, frc, x64, n, ib, diag, chunk_start(p), pc,
+            near_chunk<TENSOR, PER>(pos, frc, x64, n, ib, diag, chunk_start(p), pc,
                                          &s_i[w][0], premise, nj, test, get);
         }
         if (!diag) store_rows(s_j[w], pc.alpha_sum, nearl != 0, nj, jpart, sh, ib, p);
@@ -449,9 +274,9 @@ k_wave_f32_asm(const float4* __restrict__ pos, const float4* __restrict__ frc,
     store_sums<B>(&s_i[0][0], n, ib, s, partial);
 }
 
-hipError_t launch_wave_f32(const PairLaunch& L, int tensor, bool kahan, const float4* pos,
-                           const float4* frc, const double* x64, int n, const PairConst& pc,
-                           double* partial, hipStream_t st)
+hipError_t launch_wave_f32(const PairLaunch& L, int tensor, const float4* pos, const float4* frc,
+                           const double* x64, int n, const PairConst& pc, double* partial,
+                           hipStream_t st)
 {
     const WaveShape sh = wave_shape_of(L, n);
     double* jpart = (double*)((char*)partial + wave_jpart_offset(sh, n));
@@ -459,27 +284,14 @@ hipError_t launch_wave_f32(const PairLaunch& L, int tensor, bool kahan, const fl
     if (const hipError_t e = premise_counters(&premise); e != hipSuccess) return e;
     const dim3 grid((unsigned)(sh.nb * (sh.splits + 1))), block(256);
     const bool per = pc.box > 0.0;
-#define SD_ASM(T, P)                                                                            \
-    hipLaunchKernelGGL((k_wave_f32_asm<T, P>), grid, block, 0, st, pos, frc, x64, n, sh, pc,    \
-                       partial, jpart, premise)
-#define SD_GO(T, K, P, I, IK)                                                                   \
-    hipLaunchKernelGGL((k_wave_f32<T, K, P, I, IK>), grid, block, 0, st, pos, frc, x64, n, sh, pc, \
-                       partial, jpart, premise)
-#define SD_ILP(T, P)                                                                           \
-    do {                                                                                       \
-        if (L.ilp == 2) {                                                                      \
-            if (kahan) SD_ASM(T, P); else SD_GO(T, false, P, 2, 8);                            \
-        } else {                                                                               \
-            if (kahan) SD_GO(T, true, P, 1, 4); else SD_GO(T, false, P, 1, 4);                 \
-        }                                                                                      \
-    } while (0)
+#define SD_GO(T, P)                                                                             \
+    hipLaunchKernelGGL((k_wave_f32<T, P>), grid, block, 0, st, pos, frc, x64, n, sh, pc, partial, \
+                       jpart, premise)
     if (tensor == T_OSEEN) {
-        if (per) SD_ILP(T_OSEEN, true); else SD_ILP(T_OSEEN, false);
+        if (per) SD_GO(T_OSEEN, true); else SD_GO(T_OSEEN, false);
     } else {
-        if (per) SD_ILP(T_RPY, true); else SD_ILP(T_RPY, false);
+        if (per) SD_GO(T_RPY, true); else SD_GO(T_RPY, false);
     }
-#undef SD_ILP
-#undef SD_ASM
 #undef SD_GO
     return hipGetLastError();
 }

@@ -46,13 +46,13 @@ __device__ __forceinline__ void pair_sums(WaveI64& L, double A, double Bt, doubl
 // kernel and merge 301 us.  Near pairs only set a bit in the hot loop and are
 // evaluated after the chunk's steps: inlined in every step the branch took all
 // 256 registers.
-template <int TENSOR, bool PER, int ILP>
+template <int TENSOR, bool PER>
 __global__ void __launch_bounds__(256)
 k_wave_f64(const double4* __restrict__ pos, const double4* __restrict__ frc, int n, WaveShape sh,
            PairConst pc, double* __restrict__ partial, double* __restrict__ jpart,
            unsigned long long* __restrict__ premise)
 {
-    constexpr int B = 64 * ILP;
+    constexpr int ILP = 2, B = 64 * ILP;
     __shared__ __align__(16) double s_rec[4][32 * 6];
     __shared__ double s_j[4][4 * 48];
     __shared__ double s_i[4][3 * B];
@@ -234,19 +234,14 @@ hipError_t launch_wave_f64(const PairLaunch& L, int tensor, const double4* pos, 
     if (const hipError_t e = premise_counters(&premise); e != hipSuccess) return e;
     const dim3 grid((unsigned)(sh.nb * (sh.splits + 1))), block(256);
     const bool per = pc.box > 0.0;
-#define SD_GO(T, P, I)                                                                         \
-    hipLaunchKernelGGL((k_wave_f64<T, P, I>), grid, block, 0, st, pos, frc, n, sh, pc, partial, \
+#define SD_GO(T, P)                                                                          \
+    hipLaunchKernelGGL((k_wave_f64<T, P>), grid, block, 0, st, pos, frc, n, sh, pc, partial, \
                        jpart, premise)
-#define SD_ILP(T, P)                                                                           \
-    do {                                                                                       \
-        if (L.ilp == 2) SD_GO(T, P, 2); else SD_GO(T, P, 1);                                   \
-    } while (0)
     if (tensor == T_OSEEN) {
-        if (per) SD_ILP(T_OSEEN, true); else SD_ILP(T_OSEEN, false);
+        if (per) SD_GO(T_OSEEN, true); else SD_GO(T_OSEEN, false);
     } else {
-        if (per) SD_ILP(T_RPY, true); else SD_ILP(T_RPY, false);
+        if (per) SD_GO(T_RPY, true); else SD_GO(T_RPY, false);
     }
-#undef SD_ILP
 #undef SD_GO
     return hipGetLastError();
 }

@@ -16,8 +16,8 @@ template <typename V4>
 __global__ void __launch_bounds__(256)
 k_wave_fold(const double* __restrict__ partial, const double* __restrict__ jpart, int n, int B,
             WaveShape sh, const V4* __restrict__ frc, double mu0, double* __restrict__ vel,
-            double* __restrict__ x, double* __restrict__ v_prev, double* __restrict__ v_out,
-            double dt, int mode, V4* __restrict__ pos_next, double qs)
+            const double* x_in, double* x_out, double* __restrict__ v_prev,
+            double* __restrict__ v_out, double dt, int mode, V4* __restrict__ pos_next, double qs)
 {
     __shared__ double s_sum[8][3][32];
     const int t = threadIdx.x & 31, sl = threadIdx.x >> 5;
@@ -84,8 +84,8 @@ k_wave_fold(const double* __restrict__ partial, const double* __restrict__ jpart
     for (int c = 0; c < 3; ++c) {
         const size_t e = 3 * (size_t)i + c;
         const double inc = (mode == 2) ? (1.5 * u[c] - 0.5 * v_prev[e]) : u[c];
-        xn[c] = x[e] + dt * inc;
-        x[e] = xn[c];
+        xn[c] = x_in[e] + dt * inc;
+        x_out[e] = xn[c];
         if (mode != 0) v_prev[e] = u[c];
         if (v_out) v_out[e] = u[c];
     }
@@ -93,9 +93,9 @@ k_wave_fold(const double* __restrict__ partial, const double* __restrict__ jpart
 }
 
 hipError_t launch_wave_fold(const PairLaunch& L, bool f64, int n, const PairConst& pc,
-                            const double* partial, const void* frc, double* vel, double* x,
-                            double* v_prev, double* v_out, double dt, int mode, void* pos_next,
-                            hipStream_t st)
+                            const double* partial, const void* frc, double* vel,
+                            const double* x_in, double* x_out, double* v_prev, double* v_out,
+                            double dt, int mode, void* pos_next, hipStream_t st)
 {
     const WaveShape sh = wave_shape_of(L, n);
     const double* jpart = (const double*)((const char*)partial + wave_jpart_offset(sh, n));
@@ -103,11 +103,11 @@ hipError_t launch_wave_fold(const PairLaunch& L, bool f64, int n, const PairCons
     const double qs = pc.box > 0.0 ? 4294967296.0 / pc.box : 0.0;
     if (f64)
         hipLaunchKernelGGL((k_wave_fold<double4>), grid, block, 0, st, partial, jpart, n, 64 * L.ilp,
-                           sh, (const double4*)frc, pc.mu0, vel, x, v_prev, v_out, dt, mode,
+                           sh, (const double4*)frc, pc.mu0, vel, x_in, x_out, v_prev, v_out, dt, mode,
                            (double4*)pos_next, qs);
     else
         hipLaunchKernelGGL((k_wave_fold<float4>), grid, block, 0, st, partial, jpart, n, 64 * L.ilp,
-                           sh, (const float4*)frc, pc.mu0, vel, x, v_prev, v_out, dt, mode,
+                           sh, (const float4*)frc, pc.mu0, vel, x_in, x_out, v_prev, v_out, dt, mode,
                            (float4*)pos_next, qs);
     return hipGetLastError();
 }

@@ -1,7 +1,9 @@
-"""The wave-symmetric kernels (each pair of particles once, four waves per
-i-block) against the oracle at the sizes where their schedule changes: one
-block, odd and even block counts, ragged last blocks, the first sizes with one
-and with two particles per lane, near, overlapping and coincident pairs."""
+"""The kernels of the automatic choice for small and middle suspensions (whole
+rows in one launch; each pair of particles once in wave-symmetric blocks)
+against the oracle at the sizes where their schedules change: single
+work-groups, remainders of the rounds of 256 particles, the first sizes with two
+particles per work-group and of the wave-symmetric kernels, odd and even block
+counts, ragged last blocks, near, overlapping and coincident pairs."""
 import numpy as np
 import pytest
 
@@ -36,7 +38,8 @@ def _positions(n, box, close):
     return x, W.box_side(n, 0.05)
 
 
-@pytest.mark.parametrize("n", [1024, 1025, 1087, 1088, 1152, 3499, 3500, 3584, 3585, 3713])
+@pytest.mark.parametrize("n", [9, 255, 257, 513, 1025, 1299, 1300, 1301, 3999, 4000, 4096, 4097,
+                               4225])
 @pytest.mark.parametrize("form", ["rpy", "overlap", "oseen", "box"])
 def test_f64_product(sd, orc, n, form):
     """Velocities and premise counts of the FP64 product (1e-12: the sum of n
@@ -56,7 +59,8 @@ def test_f64_product(sd, orc, n, form):
     assert counts == tuple(orc.premise_counts(po, x))
 
 
-@pytest.mark.parametrize("n", [1024, 1025, 1088, 4999, 5000, 5120, 5121, 5249])
+@pytest.mark.parametrize("n", [9, 255, 257, 512, 513, 768, 769, 1024, 1025, 1299, 1300, 1301, 2047,
+                               5899, 5900, 6016, 6017, 6145])
 @pytest.mark.parametrize("prec", [0, 2])
 @pytest.mark.parametrize("form", ["rpy", "overlap", "oseen", "box"])
 def test_f32_product(sd, orc, n, prec, form):
@@ -78,16 +82,17 @@ def test_f32_product(sd, orc, n, prec, form):
     assert counts == tuple(orc.premise_counts(po, x))
 
 
-@pytest.mark.parametrize("n,prec,tol", [(1100, 1, 1e-12), (1100, 0, 1e-6), (5200, 0, 1e-6)])
+@pytest.mark.parametrize("n,prec,tol", [(300, 1, 1e-12), (300, 0, 1e-6), (1301, 0, 1e-6),
+                                        (4100, 1, 1e-12), (6000, 0, 1e-6)])
 @pytest.mark.parametrize("integ", [0, 1])
 @pytest.mark.parametrize("box", [False, True])
-@pytest.mark.parametrize("steps", [3, 40])
+@pytest.mark.parametrize("steps", [1, 2, 3, 40])
 def test_time_steps(sd, orc, n, prec, tol, integ, box, steps):
-    """The fold that also takes the time step, eager (3 steps) and with graph
-    replays (40), against the oracle: displacements within tol."""
+    """The kernels that also take the time step, eager (odd and even counts) and
+    with graph replays (40), against the oracle: displacements within tol."""
     import torch
     if steps == 40 and n > 2000:
-        pytest.skip("the oracle's 40 steps of the larger size take too long")
+        steps = 35   # two replays and three eager steps
     x, L = _positions(n, box, False)
     f, dt = W.gravity_forces(n) + 0.2 * W.gaussian_forces(n, seed=5), 0.002
     if prec != 1:
@@ -95,8 +100,32 @@ def test_time_steps(sd, orc, n, prec, tol, integ, box, steps):
     xd, vp = to_dev3(x), to_dev3(np.zeros_like(x))
     sd.sd_run(xd, to_dev4(f, torch.float64 if prec == 1 else torch.float32), dt, steps, v_prev=vp,
               integrator=integ, precision=prec, params=sd.params(box=L if box else None))
-    ref = orc.run(orc.params(box=L if box else None), x, f, dt, steps, integrator=integ)[0]
+    ref, vl, _ = orc.run(orc.params(box=L if box else None), x, f, dt, steps, integrator=integ)
     assert rel2(xd.cpu().numpy() - x, ref - x) <= tol
+    if integ:
+        assert rel2(vp.cpu().numpy(), vl) <= tol
+
+
+@pytest.mark.parametrize("n", [100, 1400])
+def test_steps_with_near_pairs_and_checkpoints(sd, orc, n):
+    """Overlapping spheres (their FP64 positions are read by other work-groups
+    during a step) and checkpoints at odd and even steps; sd_step continues."""
+    import torch
+    x, _ = _positions(n, False, True)
+    f, dt = W.round_to_f32(W.gaussian_forces(n, seed=8)), 0.001
+    po = orc.params(overlap=True)
+    for prec, tol in ((1, 1e-11), (0, 1e-6)):
+        fd = to_dev4(f, torch.float64 if prec == 1 else torch.float32)
+        ps = sd.params(overlap=True)
+        xd, ck = to_dev3(x), to_dev3(np.zeros((3 * n, 3)))
+        sd.sd_run(xd, fd, dt, 5, checkpoints=ck, checkpoint_every=2, precision=prec, params=ps)
+        sd.sd_step(xd, fd, dt, 5, precision=prec, params=ps)
+        ref = orc.run(po, x, f, dt, 6, stride=2)
+        got = ck.cpu().numpy().reshape(3, n, 3)
+        assert np.array_equal(got[0], x)
+        for k in (1, 2):
+            assert rel2(got[k] - x, ref[2][k] - x) <= tol
+        assert rel2(xd.cpu().numpy() - x, ref[0] - x) <= tol
 
 
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 128, 129, 193, 1000])
