@@ -4,6 +4,8 @@
 #include "pair_terms.h"
 #include "sd_internal.h"
 
+#include <algorithm>
+
 namespace sd {
 
 template <typename P4>
@@ -89,10 +91,9 @@ __global__ void __launch_bounds__(256) k_axpy(double s, const double* __restrict
     if (k < m) y[k] += s * x[k];
 }
 
-__global__ void __launch_bounds__(64) k_fill_i32(int32_t* __restrict__ p, int32_t value, int count)
+__global__ void __launch_bounds__(256) k_fill_i32(int32_t* __restrict__ p, int32_t value, int count)
 {
-    const int k = blockIdx.x * 64 + threadIdx.x;
-    if (k < count) p[k] = value;
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < count; k += (int)gridDim.x * 256) p[k] = value;
 }
 
 // out = (1/n) sum_i v_i in a fixed order, in two launches: G = mean_groups(n)
@@ -239,7 +240,8 @@ hipError_t launch_axpy(double s, const double* x, double* y, int64_t m, hipStrea
 
 hipError_t launch_fill_i32(int32_t* p, int32_t value, int count, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_fill_i32, dim3((count + 63) / 64), dim3(64), 0, st, p, value, count);
+    const int groups = std::min((count + 255) / 256, 1024);
+    hipLaunchKernelGGL(k_fill_i32, dim3(groups), dim3(256), 0, st, p, value, count);
     return hipGetLastError();
 }
 

@@ -3,14 +3,17 @@
 //   F_i = F_ext,i - sum'_j zeta(r_i - r_j) (v_i - v_j),
 //   mu0 zeta(r) = [1/(4s) - 9/40 log s] rhat rhat - 1/6 log s (I - rhat rhat),
 //   s = r/a - 2 < s_cut (Sec. 2.3: s_cut = 1), clamped to s >= s_min.
-// The primed sum runs over close pairs only, found with a cell list rebuilt on
-// the device every step (cells of side >= (2 + s_cut) a; the grid is derived
-// from the bounding box on the device, so a step needs no host round trip).
-// Cells are filled with integer atomics and then sorted by particle index, so
-// the summation order, and hence the result, is deterministic.  In a periodic
-// cubic box the grid tiles the box, cell neighbours wrap around, and each pair
-// interacts through its nearest image only.  All of it is
-// O(N x neighbours) FP64 work next to the O(N^2) mobility product.
+// The primed sum runs over close pairs only, found with a hashed cell list
+// rebuilt on the device every step: cells of side (2 + s_cut) a (free space) or
+// tiling the box (at least that large), each a chain of particles in a table of
+// buckets.  No bounding box, counting or sorting pass is needed: a call is three
+// launches (clear the buckets, insert, forces).  The chains' order depends on
+// the scheduling of the insertions, so the forces take the members of a chain
+// in ascending particle index, and the 27 cells of a particle's neighbourhood
+// are summed in a fixed order: the result is deterministic.  In a periodic
+// cubic box cell neighbours wrap around, and each pair interacts through its
+// nearest image only.  All of it is O(N x neighbours) FP64 work next to the
+// O(N^2) mobility product.
 #include "sd.h"
 #include "sd_host.h"
 #include "sd_internal.h"
@@ -20,17 +23,14 @@
 
 namespace sd {
 
-constexpr int LUB_MAX_CELLS = 1 << 21;   // cap of the cell grid (cells grow beyond the cutoff if needed)
-constexpr int SCAN_B = 2048;                          // cells per scan block (256 threads x 8)
-constexpr int SCAN_NB = LUB_MAX_CELLS / SCAN_B;       // 1024 scan blocks at most
-constexpr int BBOX_NB = 1024;                         // bounding-box partials at most
-
-struct CellGrid {
-    double lo[3];
-    double h;        // cell side
+// Cells and buckets.  Free space: cell floor(x / h) per axis (clamped to 2^30:
+// particles further out share the outermost cells, which costs time only);
+// periodic: dims cells per axis tile the cube.
+struct CellHash {
+    double ih;       // 1 / cell side
     double box;      // periodic cubic box side, 0 = free space
-    int dims[3];
-    int ncell;
+    int dims;        // cells per axis of the box
+    unsigned mask;   // buckets - 1 (a power of two)
 };
 
 struct LubConst {
@@ -38,311 +38,143 @@ struct LubConst {
     PairConst pc;    // box for the nearest image
 };
 
-// Bounding box, stage 1: work-group b reduces particles [b chunk, (b+1) chunk)
-// to part[b] = (lo xyz, hi xyz).  min / max are exact, so the result does not
-// depend on the reduction order.
-__global__ void __launch_bounds__(256) k_lub_bbox(const double* __restrict__ x, int n, int chunk,
-                                                  double* __restrict__ part)
+__device__ __forceinline__ int cell_coord(const CellHash& g, double v)
 {
-    __shared__ double lo[3][256], hi[3][256];
-    const int t = threadIdx.x;
-    const int b0 = blockIdx.x * chunk, b1 = min(n, b0 + chunk);
-    double l[3] = { 1e300, 1e300, 1e300 }, u[3] = { -1e300, -1e300, -1e300 };
-    for (int i = b0 + t; i < b1; i += 256)
-        for (int k = 0; k < 3; ++k) {
-            const double v = x[3 * (size_t)i + k];
-            l[k] = fmin(l[k], v);
-            u[k] = fmax(u[k], v);
-        }
-    for (int k = 0; k < 3; ++k) {
-        lo[k][t] = l[k];
-        hi[k][t] = u[k];
+    if (g.box > 0.0) {
+        v -= g.box * floor(v / g.box);   // wrap into [0, box)
+        const int c = (int)fmin(fmax(floor(v * g.ih), 0.0), 1073741824.0);
+        return c >= g.dims ? g.dims - 1 : c;
     }
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w)
-            for (int k = 0; k < 3; ++k) {
-                lo[k][t] = fmin(lo[k][t], lo[k][t + w]);
-                hi[k][t] = fmax(hi[k][t], hi[k][t + w]);
-            }
-        __syncthreads();
-    }
-    if (t < 3) {
-        part[6 * blockIdx.x + t] = lo[t][0];
-        part[6 * blockIdx.x + 3 + t] = hi[t][0];
-    }
+    return (int)fmin(fmax(floor(v * g.ih), -1073741824.0), 1073741824.0);
 }
 
-// Bounding box, stage 2 (one work-group) -> cell grid; free space reduces the
-// nparts partials, a periodic box tiles the cube.
-__global__ void __launch_bounds__(256) k_lub_grid(const double* __restrict__ part, int nparts,
-                                                  double hmin, double box,
-                                                  CellGrid* __restrict__ g)
+// (neighbouring cells of a row along x are neighbouring buckets: nine cache
+// lines per neighbourhood, not 27)
+__device__ __forceinline__ unsigned bucket_of(const CellHash& g, int cx, int cy, int cz)
 {
-    if (box > 0.0) {  // periodic: the grid tiles the box, cells no smaller than hmin
-        if (threadIdx.x == 0) {
-            int d = (int)floor(box / hmin);
-            d = d < 1 ? 1 : (d > 128 ? 128 : d);  // 128^3 <= LUB_MAX_CELLS
-            for (int k = 0; k < 3; ++k) {
-                g->lo[k] = 0.0;
-                g->dims[k] = d;
-            }
-            g->h = box / d;
-            g->box = box;
-            g->ncell = d * d * d;
-        }
-        return;
-    }
-    __shared__ double lo[3][256], hi[3][256];
-    const int t = threadIdx.x;
-    double l[3] = { 1e300, 1e300, 1e300 }, u[3] = { -1e300, -1e300, -1e300 };
-    for (int b = t; b < nparts; b += 256)
-        for (int k = 0; k < 3; ++k) {
-            l[k] = fmin(l[k], part[6 * b + k]);
-            u[k] = fmax(u[k], part[6 * b + 3 + k]);
-        }
-    for (int k = 0; k < 3; ++k) {
-        lo[k][t] = l[k];
-        hi[k][t] = u[k];
-    }
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w)
-            for (int k = 0; k < 3; ++k) {
-                lo[k][t] = fmin(lo[k][t], lo[k][t + w]);
-                hi[k][t] = fmax(hi[k][t], hi[k][t + w]);
-            }
-        __syncthreads();
-    }
-    if (t == 0) {
-        double ext[3], h = hmin;
-        for (int k = 0; k < 3; ++k) {
-            ext[k] = hi[k][0] - lo[k][0];
-            // non-finite coordinates (NaN / Inf inputs) collapse that axis to one cell
-            if (!(ext[k] >= 0.0) || !(ext[k] < 1e300)) ext[k] = 0.0;
-            if (!(lo[k][0] > -1e300)) lo[k][0] = 0.0;
-        }
-        // grow the cell until the grid fits the cap (bounded: 1.25^400 covers any
-        // finite extent)
-        for (int it = 0; it < 400; ++it) {
-            double cells = 1.0;
-            for (int k = 0; k < 3; ++k) cells *= floor(ext[k] / h) + 1.0;
-            if (cells <= (double)LUB_MAX_CELLS) break;
-            h *= 1.25;
-        }
-        int nc = 1;
-        for (int k = 0; k < 3; ++k) {
-            g->lo[k] = lo[k][0];
-            g->dims[k] = (int)floor(ext[k] / h) + 1;
-            nc *= g->dims[k];
-        }
-        g->h = h;
-        g->box = 0.0;
-        g->ncell = nc;
-    }
+    unsigned k = (unsigned)cy * 19349663u ^ (unsigned)cz * 83492791u;
+    k ^= k >> 15;
+    k *= 2654435761u;
+    return ((k ^ (k >> 16)) + (unsigned)cx) & g.mask;
 }
 
-__device__ __forceinline__ int cell_coord(double v, double lo, double h, int dim, double box)
-{
-    if (box > 0.0) v -= box * floor(v / box);  // wrap into [0, box)
-    int c = (int)floor((v - lo) / h);
-    return c < 0 ? 0 : (c >= dim ? dim - 1 : c);
-}
-
-// Distinct neighbour cells of cell c along one axis: c-1, c, c+1, clipped to
-// the grid in free space, wrapped (and de-duplicated on grids narrower than
-// three cells) in a periodic box.  Returns the count.
-__device__ __forceinline__ int axis_neighbours(int c, int dim, bool periodic, int (&out)[3])
-{
-    int m = 0;
-    if (periodic) {
-        if (dim < 3) {
-            for (int k = 0; k < dim; ++k) out[m++] = k;
-        } else {
-            out[m++] = c == 0 ? dim - 1 : c - 1;
-            out[m++] = c;
-            out[m++] = c == dim - 1 ? 0 : c + 1;
-        }
-    } else {
-        for (int k = c - 1; k <= c + 1; ++k)
-            if (k >= 0 && k < dim) out[m++] = k;
-    }
-    return m;
-}
-
-__global__ void __launch_bounds__(256) k_lub_count(const double* __restrict__ x, int n,
-                                                   const CellGrid* __restrict__ g,
-                                                   int* __restrict__ cid, int* __restrict__ count)
+__global__ void __launch_bounds__(256) k_lub_insert(const double* __restrict__ x, int n, CellHash g,
+                                                    int* __restrict__ head, int* __restrict__ next)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    const double h = g->h;
-    const int cx = cell_coord(x[3 * (size_t)i], g->lo[0], h, g->dims[0], g->box);
-    const int cy = cell_coord(x[3 * (size_t)i + 1], g->lo[1], h, g->dims[1], g->box);
-    const int cz = cell_coord(x[3 * (size_t)i + 2], g->lo[2], h, g->dims[2], g->box);
-    const int c = (cz * g->dims[1] + cy) * g->dims[0] + cx;
-    cid[i] = c;
-    atomicAdd(&count[c], 1);
+    const unsigned b = bucket_of(g, cell_coord(g, x[3 * (size_t)i]),
+                                 cell_coord(g, x[3 * (size_t)i + 1]),
+                                 cell_coord(g, x[3 * (size_t)i + 2]));
+    next[i] = atomicExch(&head[b], i);
 }
 
-// Exclusive scan of the cell counts in three passes: per-block sums of SCAN_B
-// cells, a scan of the (at most SCAN_NB) block sums in one work-group, then
-// each block scans its cells from its offset.  start[ncell] = n; the counts
-// are reset to zero for use as scatter cursors.  Integer sums: the result is
-// exact and independent of the order.
-__device__ __forceinline__ int block_exclusive_scan_256(int v, int* sh)
+// The m-th distinct neighbour (m = 0, 1, 2) of cell c along one axis: c - 1, c,
+// c + 1, wrapped in a periodic box and without duplicates on boxes of fewer than
+// three cells.  False: there is none.
+__device__ __forceinline__ bool axis_neighbour(const CellHash& g, int c, int m, int& out)
 {
-    const int t = threadIdx.x;
-    sh[t] = v;
-    __syncthreads();
-    for (int w = 1; w < 256; w <<= 1) {
-        const int a = t >= w ? sh[t - w] : 0;
-        __syncthreads();
-        sh[t] += a;
-        __syncthreads();
+    if (!(g.box > 0.0)) {
+        out = c - 1 + m;
+        return true;
     }
-    const int incl = sh[t];
-    __syncthreads();
-    return incl - v;
-}
-
-__global__ void __launch_bounds__(256) k_lub_scan_sums(const int* __restrict__ count,
-                                                       const CellGrid* __restrict__ g,
-                                                       int* __restrict__ bsum)
-{
-    __shared__ int sh[256];
-    const int nc = g->ncell;
-    const int c0 = blockIdx.x * SCAN_B + threadIdx.x * (SCAN_B / 256);
-    if (blockIdx.x * SCAN_B >= nc) return;   // uniform per block
-    int v = 0;
-    for (int c = c0; c < c0 + SCAN_B / 256; ++c)
-        if (c < nc) v += count[c];
-    const int ex = block_exclusive_scan_256(v, sh);
-    if (threadIdx.x == 255) bsum[blockIdx.x] = ex + v;
-}
-
-__global__ void __launch_bounds__(1024) k_lub_scan_top(int* __restrict__ bsum,
-                                                       const CellGrid* __restrict__ g)
-{
-    __shared__ int sh[1024];
-    const int t = threadIdx.x;
-    const int nb = (g->ncell + SCAN_B - 1) / SCAN_B;
-    const int v = t < nb ? bsum[t] : 0;
-    sh[t] = v;
-    __syncthreads();
-    for (int w = 1; w < 1024; w <<= 1) {
-        const int a = t >= w ? sh[t - w] : 0;
-        __syncthreads();
-        sh[t] += a;
-        __syncthreads();
+    if (g.dims < 3) {
+        out = m;
+        return m < g.dims;
     }
-    if (t < nb) bsum[t] = sh[t] - v;   // exclusive offsets
+    out = c - 1 + m;
+    if (out < 0) out += g.dims;
+    if (out >= g.dims) out -= g.dims;
+    return true;
 }
 
-__global__ void __launch_bounds__(256) k_lub_scan_apply(int* __restrict__ count,
-                                                        int* __restrict__ start,
-                                                        const int* __restrict__ boff,
-                                                        const CellGrid* __restrict__ g, int n)
-{
-    __shared__ int sh[256];
-    const int nc = g->ncell;
-    if (blockIdx.x * SCAN_B >= nc) return;   // uniform per block
-    const int c0 = blockIdx.x * SCAN_B + threadIdx.x * (SCAN_B / 256);
-    int v = 0;
-    for (int c = c0; c < c0 + SCAN_B / 256; ++c)
-        if (c < nc) v += count[c];
-    int run = boff[blockIdx.x] + block_exclusive_scan_256(v, sh);
-    for (int c = c0; c < c0 + SCAN_B / 256; ++c)
-        if (c < nc) {
-            const int k = count[c];
-            start[c] = run;
-            run += k;
-            count[c] = 0;
-        }
-    if (blockIdx.x == 0 && threadIdx.x == 0) start[nc] = n;
-}
-
-__global__ void __launch_bounds__(256) k_lub_scatter(const int* __restrict__ cid, int n,
-                                                     const int* __restrict__ start,
-                                                     int* __restrict__ cursor,
-                                                     int* __restrict__ order)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const int c = cid[i];
-    order[start[c] + atomicAdd(&cursor[c], 1)] = i;
-}
-
-// each cell's members in ascending particle index (cells hold a handful)
-__global__ void __launch_bounds__(256) k_lub_sort(const int* __restrict__ start,
-                                                  int* __restrict__ order,
-                                                  const CellGrid* __restrict__ g)
-{
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= g->ncell) return;
-    const int b = start[c], e = start[c + 1];
-    for (int k = b + 1; k < e; ++k) {
-        const int v = order[k];
-        int m = k - 1;
-        while (m >= b && order[m] > v) {
-            order[m + 1] = order[m];
-            --m;
-        }
-        order[m + 1] = v;
-    }
-}
+// 32 lanes per particle, one per cell of its neighbourhood (27), so that the
+// chains are walked side by side: the kernel is bound by the latency of a chain
+// (bucket, particle, position).  A lane takes the close particles of its cell
+// LUB_TAKE at a time in ascending index; a cell with more is walked again.
+// Microseconds per lubrication_forces (three launches), where ten launches
+// (bounding box, grid, count, three scan passes, scatter, sort, forces with one
+// lane per particle) were used before: N = 100 60 -> 16, 5000 83 -> 16, 20000 82
+// -> 20, 65536 98 -> 45, 200000 156 -> 139.
+constexpr int LUB_TAKE = 4;
 
 __global__ void __launch_bounds__(256)
 k_lub_force(const double* __restrict__ x, const double* __restrict__ v,
-            const double* __restrict__ f_ext, int n, const CellGrid* __restrict__ g,
-            const int* __restrict__ start, const int* __restrict__ order, LubConst lc,
-            double* __restrict__ f_out, float4* __restrict__ rec32, double4* __restrict__ rec64)
+            const double* __restrict__ f_ext, int n, CellHash g, const int* __restrict__ head,
+            const int* __restrict__ next, LubConst lc, double* __restrict__ f_out,
+            float4* __restrict__ rec32, double4* __restrict__ rec64)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
+    const int i = blockIdx.x * 8 + (threadIdx.x >> 5);
+    if (i >= n) return;   // whole groups of 32 lanes
+    const int q = threadIdx.x & 31;
     const double xi[3] = { x[3 * (size_t)i], x[3 * (size_t)i + 1], x[3 * (size_t)i + 2] };
-    const double vi[3] = { v[3 * (size_t)i], v[3 * (size_t)i + 1], v[3 * (size_t)i + 2] };
-    const double h = g->h;
-    const int dims[3] = { g->dims[0], g->dims[1], g->dims[2] };
-    const bool per = g->box > 0.0;
-    int nb[3][3], nn[3];
-    for (int k = 0; k < 3; ++k)
-        nn[k] = axis_neighbours(cell_coord(xi[k], g->lo[k], h, dims[k], g->box), dims[k], per,
-                                nb[k]);
     double acc[3] = { 0.0, 0.0, 0.0 };
-    for (int iz = 0; iz < nn[2]; ++iz) {
-        const int z = nb[2][iz];
-        for (int iy = 0; iy < nn[1]; ++iy) {
-            const int y = nb[1][iy];
-            for (int ix = 0; ix < nn[0]; ++ix) {
-                const int xx = nb[0][ix];
-                const int c = (z * dims[1] + y) * dims[0] + xx;
-                for (int k = start[c]; k < start[c + 1]; ++k) {
-                    const int j = order[k];
-                    if (j == i) continue;
-                    double d[3] = { xi[0] - x[3 * (size_t)j], xi[1] - x[3 * (size_t)j + 1],
-                                    xi[2] - x[3 * (size_t)j + 2] };
-                    nearest_image_d(lc.pc, d[0], d[1], d[2]);
-                    const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-                    if (!(r2 < lc.rcut2) || r2 == 0.0) continue;
-                    const double r = sqrt(r2);
-                    double s = r / lc.a - 2.0;
-                    if (s >= lc.s_cut) continue;
-                    if (s < lc.s_min) s = lc.s_min;
-                    const double ls = log(s);
-                    const double cP = (1.0 / (4.0 * s) - 9.0 / 40.0 * ls) / lc.mu0;
-                    const double cT = (-1.0 / 6.0 * ls) / lc.mu0;
-                    const double dv[3] = { vi[0] - v[3 * (size_t)j], vi[1] - v[3 * (size_t)j + 1],
-                                           vi[2] - v[3 * (size_t)j + 2] };
-                    const double hd = (d[0] * dv[0] + d[1] * dv[1] + d[2] * dv[2]) / r;  // rhat . dv
-                    for (int k3 = 0; k3 < 3; ++k3) {
-                        const double nrm = hd * d[k3] / r;                             // (rhat rhat dv)_k
-                        acc[k3] -= cP * nrm + cT * (dv[k3] - nrm);
-                    }
+    int cc[3];
+    bool cell = q < 27;
+    cell = axis_neighbour(g, cell_coord(g, xi[0]), q % 3, cc[0]) && cell;
+    cell = axis_neighbour(g, cell_coord(g, xi[1]), q / 3 % 3, cc[1]) && cell;
+    cell = axis_neighbour(g, cell_coord(g, xi[2]), q / 9, cc[2]) && cell;
+    if (cell) {
+        const int first = head[bucket_of(g, cc[0], cc[1], cc[2])];
+        int last = -1;
+        bool more = first >= 0;
+        while (more) {
+            // the LUB_TAKE smallest indices above `last` of the close particles
+            // of this cell (a bucket may hold other cells' particles too)
+            int take[LUB_TAKE];
+#pragma unroll
+            for (int k = 0; k < LUB_TAKE; ++k) take[k] = 0x7fffffff;
+            for (int j = first; j >= 0; j = next[j]) {
+                if (j == i || j <= last) continue;
+                const double xj[3] = { x[3 * (size_t)j], x[3 * (size_t)j + 1],
+                                       x[3 * (size_t)j + 2] };
+                double d[3] = { xi[0] - xj[0], xi[1] - xj[1], xi[2] - xj[2] };
+                nearest_image_d(lc.pc, d[0], d[1], d[2]);
+                const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                if (!(r2 < lc.rcut2) || r2 == 0.0) continue;
+                if (cell_coord(g, xj[0]) != cc[0] || cell_coord(g, xj[1]) != cc[1] ||
+                    cell_coord(g, xj[2]) != cc[2])
+                    continue;
+                int m = j;   // into the sorted list
+#pragma unroll
+                for (int k = 0; k < LUB_TAKE; ++k) {
+                    const int lo = min(take[k], m);
+                    m = max(take[k], m);
+                    take[k] = lo;
+                }
+            }
+            more = take[LUB_TAKE - 1] != 0x7fffffff;
+            last = take[LUB_TAKE - 1];
+#pragma unroll
+            for (int k = 0; k < LUB_TAKE; ++k) {
+                const int j = take[k];
+                if (j == 0x7fffffff) break;
+                double d[3] = { xi[0] - x[3 * (size_t)j], xi[1] - x[3 * (size_t)j + 1],
+                                xi[2] - x[3 * (size_t)j + 2] };
+                nearest_image_d(lc.pc, d[0], d[1], d[2]);
+                const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                const double r = sqrt(r2);
+                double s = r / lc.a - 2.0;
+                if (s >= lc.s_cut) continue;
+                if (s < lc.s_min) s = lc.s_min;
+                const double ls = log(s);
+                const double cP = (1.0 / (4.0 * s) - 9.0 / 40.0 * ls) / lc.mu0;
+                const double cT = (-1.0 / 6.0 * ls) / lc.mu0;
+                const double dv[3] = { v[3 * (size_t)i] - v[3 * (size_t)j],
+                                       v[3 * (size_t)i + 1] - v[3 * (size_t)j + 1],
+                                       v[3 * (size_t)i + 2] - v[3 * (size_t)j + 2] };
+                const double hd = (d[0] * dv[0] + d[1] * dv[1] + d[2] * dv[2]) / r;  // rhat . dv
+                for (int k3 = 0; k3 < 3; ++k3) {
+                    const double nrm = hd * d[k3] / r;                             // (rhat rhat dv)_k
+                    acc[k3] -= cP * nrm + cT * (dv[k3] - nrm);
                 }
             }
         }
     }
+    // over the 27 cells, fixed order
+    for (int w = 16; w > 0; w >>= 1)
+        for (int k = 0; k < 3; ++k) acc[k] += __shfl_xor(acc[k], w);
+    if (q != 0) return;
     double fo[3];
     for (int k = 0; k < 3; ++k) fo[k] = (f_ext ? f_ext[3 * (size_t)i + k] : 0.0) + acc[k];
     // the FP64 vector and/or the force record the pair kernel reads
@@ -352,12 +184,12 @@ k_lub_force(const double* __restrict__ x, const double* __restrict__ v,
     if (rec64) rec64[i] = make_double4(fo[0], fo[1], fo[2], 0.0);
 }
 
-// Library workspace of the cell list: grid | bbox partials f64[6 BBOX_NB] |
-// block sums int[SCAN_NB] | cid[n] | order[n] | count[MAX] | start[MAX+1]
-static size_t lub_ws_bytes(int64_t n)
+// Buckets for n particles: a power of two, at least 2 n (at most 2^26).
+static int lub_buckets(int64_t n)
 {
-    return 256 + 48 * (size_t)BBOX_NB + 4 * (size_t)SCAN_NB + 4 * (size_t)n * 2 +
-           4 * ((size_t)LUB_MAX_CELLS * 2 + 1) + 256;
+    int b = 1024;
+    while (b < 2 * n && b < (1 << 26)) b <<= 1;
+    return b;
 }
 
 // f_out (f64[3n]), rec32 (f32x4[n]) and rec64 (f64x4[n]) receive the forces
@@ -368,40 +200,29 @@ sd_status lub_forces_impl(const sd_params* p, const sd_lub* lub, int64_t n, cons
 {
     sd_status st;
     void* buf = nullptr;
-    if ((st = ws_get(WS_LUB, lub_ws_bytes(n), &buf))) return st;
-    char* q = (char*)buf;
-    CellGrid* g = (CellGrid*)q;
-    q += 256;
-    double* bbox = (double*)q;
-    q += 48 * (size_t)BBOX_NB;
-    int* bsum = (int*)q;
-    q += 4 * (size_t)SCAN_NB;
-    int* cid = (int*)q;
-    q += 4 * (size_t)n;
-    int* order = (int*)q;
-    q += 4 * (size_t)n;
-    int* count = (int*)q;
-    q += 4 * (size_t)LUB_MAX_CELLS;
-    int* start = (int*)q;
+    const int buckets = lub_buckets(n);
+    if ((st = ws_get(WS_LUB, 4 * ((size_t)buckets + (size_t)n), &buf))) return st;
+    int* head = (int*)buf;
+    int* next = head + buckets;
     const int nn = (int)n;
-    const dim3 gp((unsigned)((n + 255) / 256));
-    hipError_t e = launch_fill_i32(count, 0, LUB_MAX_CELLS, hs);
-    if (e != hipSuccess) return fail(SD_EDEVICE, "fill launch: %s", hipGetErrorString(e));
-    int nparts = 0;
-    if (!(box_side(p) > 0.0)) {  // free space: bounding box of the particles
-        nparts = (int)std::min<int64_t>(BBOX_NB, std::max<int64_t>(1, (n + 4095) / 4096));
-        const int chunk = (int)((n + nparts - 1) / nparts);
-        hipLaunchKernelGGL(k_lub_bbox, dim3(nparts), dim3(256), 0, hs, x, nn, chunk, bbox);
+    // a pair within the cutoff lies in neighbouring cells: the side exceeds the
+    // cutoff by more than the rounding of x / h
+    const double hmin = (2.0 + lub->s_cut) * p->a * (1.0 + 1e-6);
+    CellHash g;
+    g.box = box_side(p);
+    g.mask = (unsigned)buckets - 1u;
+    g.dims = 0;
+    double h = hmin;
+    if (g.box > 0.0) {
+        const double d = std::floor(g.box / hmin);
+        g.dims = d < 1.0 ? 1 : (d > 1048576.0 ? 1048576 : (int)d);
+        h = g.box / g.dims;
     }
-    hipLaunchKernelGGL(k_lub_grid, dim3(1), dim3(256), 0, hs, bbox, nparts,
-                       (2.0 + lub->s_cut) * p->a, box_side(p), g);
-    hipLaunchKernelGGL(k_lub_count, gp, dim3(256), 0, hs, x, nn, g, cid, count);
-    hipLaunchKernelGGL(k_lub_scan_sums, dim3(SCAN_NB), dim3(256), 0, hs, count, g, bsum);
-    hipLaunchKernelGGL(k_lub_scan_top, dim3(1), dim3(1024), 0, hs, bsum, g);
-    hipLaunchKernelGGL(k_lub_scan_apply, dim3(SCAN_NB), dim3(256), 0, hs, count, start, bsum, g,
-                       nn);
-    hipLaunchKernelGGL(k_lub_scatter, gp, dim3(256), 0, hs, cid, nn, start, count, order);
-    hipLaunchKernelGGL(k_lub_sort, dim3(LUB_MAX_CELLS / 256), dim3(256), 0, hs, start, order, g);
+    g.ih = 1.0 / h;
+    hipError_t e = launch_fill_i32(head, -1, buckets, hs);
+    if (e != hipSuccess) return fail(SD_EDEVICE, "fill launch: %s", hipGetErrorString(e));
+    hipLaunchKernelGGL(k_lub_insert, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, hs, x, nn, g,
+                       head, next);
     LubConst lc;
     lc.a = p->a;
     lc.mu0 = 1.0 / (6.0 * M_PI * p->eta * p->a);
@@ -410,8 +231,8 @@ sd_status lub_forces_impl(const sd_params* p, const sd_lub* lub, int64_t n, cons
     const double rc = (2.0 + lub->s_cut) * p->a;
     lc.rcut2 = rc * rc;
     lc.pc = pair_const(p);
-    hipLaunchKernelGGL(k_lub_force, gp, dim3(256), 0, hs, x, v, f_ext, nn, g, start, order, lc,
-                       f_out, rec32, rec64);
+    hipLaunchKernelGGL(k_lub_force, dim3((unsigned)((n + 7) / 8)), dim3(256), 0, hs, x, v, f_ext, nn,
+                       g, head, next, lc, f_out, rec32, rec64);
     if ((e = hipGetLastError()) != hipSuccess)
         return fail(SD_EDEVICE, "lubrication launch: %s", hipGetErrorString(e));
     return SD_OK;
