@@ -470,7 +470,7 @@ def sd_membench(kind: int, access: int, inp, out=None, stream=None):
 
 
 def sd_set_graph_mode(mode: int) -> None:
-    """sd_run launch mode: 0 eager, 1 graphs for small n (default), 2 graphs always."""
+    """sd_run launch mode: 0 eager, 1 whichever is faster (default), 2 graphs always."""
     check(lib().sd_set_graph_mode(int(mode)))
 
 

@@ -543,9 +543,8 @@ size_t partial_bytes(const PairLaunch& L, int64_t n)
 
 // ------------------------------------------------------- graph-captured loop
 //
-// The time loop of sd_run is launch-bound for small n (two short kernels per
-// step).  Chunks of RUN_CHUNK steps [stage, (pair kernel, merge + integrate
-// + staging) x RUN_CHUNK] are captured once into a HIP graph on a private
+// With sd_set_graph_mode(2), chunks of RUN_CHUNK steps [stage, the kernels of
+// RUN_CHUNK steps] of sd_run are captured once into a HIP graph on a private
 // capture stream and replayed on the caller's stream; a chunk holds only
 // kernel nodes.  The graph is cached per device and rebuilt when anything it
 // captured changes (pointers, sizes, parameters, launch shape, workspace).
@@ -578,8 +577,12 @@ struct RunGraph {
 
 std::mutex g_rg_mu;
 std::map<int, RunGraph> g_rg;
-std::atomic<int32_t> g_graph_mode{ 1 };   // 0 off, 1 automatic (n <= RUN_GRAPH_AUTO_N), 2 always
-constexpr int64_t RUN_GRAPH_AUTO_N = 16384;
+// 0 off, 1 automatic, 2 always.  Automatic launches every kernel: replays are no
+// faster at any size (96 Euler steps, launched / replayed, us: N = 8 341 / 356,
+// 256 352 / 366, 1000 495 / 523, 5324 2385 / 2411), since the host launches a
+// step in less time than the step takes, and a run on other buffers than the
+// last captures and instantiates again.
+std::atomic<int32_t> g_graph_mode{ 1 };
 
 // Waits for the last replay before the executable graph is destroyed (a
 // rebuild may come from a call on another stream).
@@ -714,7 +717,7 @@ sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, do
     int64_t done = 0;
     const int32_t gmode = g_graph_mode.load();
     const bool graphed = !x_checkpoints && !g_prof.on && steps >= 2 * RUN_CHUNK &&
-                         (gmode == 2 || (gmode == 1 && n <= RUN_GRAPH_AUTO_N));
+                         gmode == 2;
     if (graphed) {
         // the first AB2 step (an Euler step that stores v_prev) stays eager
         if (integrator == SD_AB2 && step0 == 0) {

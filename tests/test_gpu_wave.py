@@ -98,8 +98,13 @@ def test_time_steps(sd, orc, n, prec, tol, integ, box, steps):
     if prec != 1:
         f = W.round_to_f32(f)
     xd, vp = to_dev3(x), to_dev3(np.zeros_like(x))
-    sd.sd_run(xd, to_dev4(f, torch.float64 if prec == 1 else torch.float32), dt, steps, v_prev=vp,
-              integrator=integ, precision=prec, params=sd.params(box=L if box else None))
+    sd.sd_set_graph_mode(2 if steps >= 35 else 1)
+    try:
+        sd.sd_run(xd, to_dev4(f, torch.float64 if prec == 1 else torch.float32), dt, steps,
+                  v_prev=vp, integrator=integ, precision=prec,
+                  params=sd.params(box=L if box else None))
+    finally:
+        sd.sd_set_graph_mode(1)
     ref, vl, _ = orc.run(orc.params(box=L if box else None), x, f, dt, steps, integrator=integ)
     assert rel2(xd.cpu().numpy() - x, ref - x) <= tol
     if integ:
