@@ -48,15 +48,7 @@ k_merge_integrate(const double* __restrict__ partial, int S, int n, const F4* __
     double v[3] = { mu0 * (double)f.x, mu0 * (double)f.y, mu0 * (double)f.z };
     add_split_rows(partial, S, n, i, v[0], v[1], v[2]);
     double xn[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const size_t e = 3 * (size_t)i + k;
-        const double inc = (mode == 2) ? (1.5 * v[k] - 0.5 * v_prev[e]) : v[k];
-        xn[k] = x_in[e] + dt * inc;
-        x_out[e] = xn[k];
-        if (mode != 0) v_prev[e] = v[k];
-        if (v_out) v_out[e] = v[k];
-    }
+    step_particle({ x_in, x_out, v_prev, v_out, dt, mode }, i, v, xn);
     if (pos_next) put_pos(pos_next, i, xn[0], xn[1], xn[2], qs);
 }
 

@@ -17,6 +17,7 @@
 #include "premise.h"
 #include "sd_internal.h"
 #include "sym_chunk_asm.h"
+#include "wave_sym.h"
 
 #include <algorithm>
 #include <cmath>
@@ -56,11 +57,11 @@ PairLaunch shape_pair_launch(int n, int variant, int block, int splits, int ilp,
     L.acc = 0;
     L.cus = 0;
     if (variant == 2) {
-        // rows: the symmetric splits, the diagonal blocks, the folded j side
+        // rows: the symmetric splits, the diagonal blocks
         L.jchunk = splits < 1 ? 1 : splits;
         L.cus = cus;
         const SymShape sh = sym_shape(n, block * ilp, L.jchunk, sym_slots(block, cus));
-        L.splits = sh.isplits + 2;
+        L.splits = sh.isplits + 1;
         return L;
     }
     if (splits < 1) splits = 1;
@@ -528,8 +529,7 @@ k_pair_f32_smem(const float4* __restrict__ pos, const float4* __restrict__ frc,
 // reduction is needed.  After a chunk each row stores its 16 j-side sums in
 // LDS; at the end of a tile the rows are added in FP64 in a fixed order and
 // written as FP32 j-side partials jpart[c][I][p] (scaled units), which
-// k_sym_fold_near adds in FP64, in a fixed order, into one more split row
-// (or, for a product, straight into the merged velocities).
+// k_sym_fold_near adds in FP64, in a fixed order, to the split rows.
 // Tiles are double-buffered: the next tile is read from HBM while the
 // current one is consumed, so a tile costs two barriers.
 //
@@ -1366,30 +1366,50 @@ k_pair_f32_sym_asm(const float4* __restrict__ pos, const float4* __restrict__ fr
     sym_lanes_store<ILP, BLOCK>(L, n, ib, s, pc.alpha_sum, partial);
 }
 
-// Last split row of variant 2, one wave per run S of SYM_RUN particles
-// (lane: particle q = S SYM_RUN + lane, at offset o of its block J):
-//  * the j side: the FP32 partials of the blocks I that took block J,
-//    added in FP64 in a fixed order (I = J - 1, J - 2, ..., then the
-//    antipode), times alpha_sum;
+// The end of a product or time step of variant 2: the split rows, the j side and
+// the near pairs of a run S of SYM_RUN particles (lane: particle q = S SYM_RUN +
+// lane, at offset o of its block J), each shared by the four waves of a
+// work-group:
+//  * the split rows, in FP64;
+//  * the j side: the FP32 partials of the blocks I that took block J (I = J - 1,
+//    J - 2, ..., then the antipode), added in FP64, times alpha_sum;
 //  * the near pairs: every candidate the near flags name (see below) below
 //    the FP32 near threshold (the test of the pair kernel, so exactly the
-//    masked pairs), j != q, evaluated in FP64 (near_term) in the order of
-//    the candidate list.
+//    masked pairs), j != q, evaluated in FP64 (near_term).
+// Every wave takes its share in a fixed order and the four sums are added in wave
+// order.  Then velocities (vel given) or the time step: other work-groups read
+// the positions of near particles, so st.x_out and pos_next are other arrays than
+// x64 and pos.
+//
+// Bound by the partials (122 MB at N = 65536) where no pair is near, else by the
+// latency of the chains flag - candidate - record, which is why four waves walk
+// them.  Microseconds per AB2 step, one wave per run and k_merge_integrate after
+// it -> this: N = 16384 133 -> 126, 20000 180 -> 171, 65536 1481 -> 1470; with 0.4
+// near partners per particle 202 -> 158, 257 -> 206, 1571 -> 1531.
 template <int TENSOR, bool PER>
-__global__ void __launch_bounds__(SYM_RUN)
+__global__ void __launch_bounds__(4 * SYM_RUN)
 k_sym_fold_near(const float* __restrict__ jpart, const float4* __restrict__ pos,
                 const float4* __restrict__ frc, const double* __restrict__ x64, int n, int B,
                 int wpb, SymShape sh, PairConst pc, const uint8_t* __restrict__ flags,
-                double* __restrict__ out, const double* __restrict__ partial, double mu0,
-                double* __restrict__ vel)
+                const double* __restrict__ partial, double* __restrict__ vel, StepOut st,
+                float4* __restrict__ pos_next, double qs)
 {
-    constexpr int FOLD_CAP = 256;   // candidates listed before their records are loaded
-    __shared__ float4 s_pos[FOLD_CAP];
-    __shared__ float4 s_frc[FOLD_CAP];
-    __shared__ double s_x64[3 * FOLD_CAP];   // FP64 positions when x64 is given
-    __shared__ int s_idx[FOLD_CAP];
-    // one wave per run S of SYM_RUN particles; particle q at offset o of block J
-    const int S = blockIdx.x, lane = threadIdx.x;
+    constexpr int NW = 4;           // waves
+    constexpr int FOLD_CAP = 128;   // candidates a wave lists before their records are loaded
+    __shared__ float4 s_pos_w[NW][FOLD_CAP];
+    __shared__ float4 s_frc_w[NW][FOLD_CAP];
+    __shared__ double s_x64_w[NW][3 * FOLD_CAP];   // FP64 positions when x64 is given
+    __shared__ int s_idx_w[NW][FOLD_CAP];
+    __shared__ uint16_t s_pair_w[NW][SYM_RUN];
+    __shared__ double s_sum[NW][3][SYM_RUN];       // (first the terms of a list of pairs)
+    // particle q of run S at offset o of block J
+    const int S = blockIdx.x, lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    float4* const s_pos = s_pos_w[wv];
+    float4* const s_frc = s_frc_w[wv];
+    double* const s_x64 = s_x64_w[wv];
+    int* const s_idx = s_idx_w[wv];
+    uint16_t* const s_pair = s_pair_w[wv];
     const int q = S * SYM_RUN + lane;
     const int J = (S * SYM_RUN) / B;
     const int o = q - J * B;
@@ -1397,16 +1417,16 @@ k_sym_fold_near(const float* __restrict__ jpart, const float4* __restrict__ pos,
     const size_t cs = (size_t)nb * (size_t)sh.lmax;
     double v0 = 0.0, v1 = 0.0, v2 = 0.0;
     if (q < n) {
-        // blocks I = J - d (d = 1 .. h) in that order, the loads of a group of
-        // them issued before its adds
+        // every fourth block I = J - d (d = 1 .. h), the loads of a group of them
+        // issued before its adds
         constexpr int G = 8;
-        for (int d0 = 1; d0 <= sh.h; d0 += G) {
+        for (int d0 = 1 + wv; d0 <= sh.h; d0 += NW * G) {
             float a[G][3];
 #pragma unroll
             for (int u = 0; u < G; ++u) {
-                const int d = d0 + u;
+                const int d = d0 + NW * u;
                 if (d <= sh.h) {
-                    const int I = (J - d + nb) % nb;
+                    const int I = J - d < 0 ? J - d + nb : J - d;
                     const size_t at = (size_t)I * sh.lmax + (size_t)(d - 1) * B + o;
                     a[u][0] = jpart[at];
                     a[u][1] = jpart[cs + at];
@@ -1415,14 +1435,14 @@ k_sym_fold_near(const float* __restrict__ jpart, const float4* __restrict__ pos,
             }
 #pragma unroll
             for (int u = 0; u < G; ++u) {
-                if (d0 + u <= sh.h) {
+                if (d0 + NW * u <= sh.h) {
                     v0 += (double)a[u][0];
                     v1 += (double)a[u][1];
                     v2 += (double)a[u][2];
                 }
             }
         }
-        if (sh.extra) {
+        if (sh.extra && wv == 0) {
             const int I = (J + half) % nb;
             if (I < half) {
                 const size_t at = (size_t)I * sh.lmax + (size_t)sh.h * B + o;
@@ -1435,11 +1455,15 @@ k_sym_fold_near(const float* __restrict__ jpart, const float4* __restrict__ pos,
     v0 *= pc.alpha_sum;
     v1 *= pc.alpha_sum;
     v2 *= pc.alpha_sum;
-    // near pairs of q.  The flags name candidate particles; they are listed in
-    // LDS in a fixed order (the diagonal block, the flagged chunks of the tiles
-    // in the row of q's wave: q's block as i-block, then the flagged lanes of
-    // the waves of preceding blocks whose entry for q's tile names a chunk of
-    // q's run: q's block as j-block), their records are loaded together once
+    if (q < n) {   // a quarter of the split rows
+        const int rows = sh.isplits + 1, r0 = rows * wv / NW;
+        add_split_rows(partial + 3 * (size_t)n * r0, rows * (wv + 1) / NW - r0, n, q, v0, v1, v2);
+    }
+    // near pairs of q.  The flags name candidate particles; each wave lists its
+    // share of them in its LDS in a fixed order (wave 0: the diagonal block; the
+    // flagged chunks of the tiles in the row of q's wave: q's block as i-block;
+    // the flagged lanes of the waves of preceding blocks whose entry for q's tile
+    // names a chunk of q's run: q's block as j-block; every fourth entry), their records are loaded together once
     // FOLD_CAP are listed or the list ends, and every q tests every listed
     // candidate (the FP32 threshold test again, then FP64).  A pair of
     // different blocks lies in the virtual range of exactly one of the two,
@@ -1460,8 +1484,47 @@ k_sym_fold_near(const float* __restrict__ jpart, const float4* __restrict__ pos,
     }
     int cnt = 0;   // listed candidates (the same in every lane)
     uint32_t psub = 0, pco = 0;   // this lane's pairs against the premise r >= 2a
-    auto flush = [&]() {
-        __syncthreads();
+    // the terms of the np listed pairs (lane of q, candidate), one pair per lane,
+    // then every q takes its own in the order of the list
+    auto pair_terms = [&](int np) __attribute__((always_inline)) {
+        wave_lds_fence();
+        const int pr = lane < np ? (int)s_pair[lane] : 0;
+        const int ql = pr & 63, e = pr >> 8;
+        double y0 = __shfl(xq64[0], ql), y1 = __shfl(xq64[1], ql), y2 = __shfl(xq64[2], ql);
+        const float yx = __shfl(xq, ql), yy = __shfl(yq, ql), yz = __shfl(zq, ql);
+        if (lane < np) {
+            const int jg = s_idx[e], qg = S * SYM_RUN + ql;
+            const float4 pj = s_pos[e], fj = s_frc[e];
+            double d0, d1, d2, t0 = 0.0, t1 = 0.0, t2 = 0.0;
+            if (x64) {   // the FP64 positions, staged
+                d0 = y0 - s_x64[3 * e];
+                d1 = y1 - s_x64[3 * e + 1];
+                d2 = y2 - s_x64[3 * e + 2];
+                if (PER) nearest_image_d(pc, d0, d1, d2);
+            } else {
+                near_diff_v<PER>(yx, yy, yz, qg, pj, jg, pc, nullptr, d0, d1, d2);
+            }
+            const int cls = near_term<TENSOR>(pc, d0, d1, d2, (double)fj.x, (double)fj.y,
+                                              (double)fj.z, t0, t1, t2);
+            if (qg < jg) {
+                psub += cls == PREMISE_SUB2A;
+                pco += cls == PREMISE_COINCIDENT;
+            }
+            s_sum[wv][0][lane] = t0;
+            s_sum[wv][1][lane] = t1;
+            s_sum[wv][2][lane] = t2;
+        }
+        wave_lds_fence();
+        for (int k = 0; k < np; ++k)
+            if ((s_pair[k] & 63) == lane) {
+                v0 += s_sum[wv][0][k];
+                v1 += s_sum[wv][1][k];
+                v2 += s_sum[wv][2][k];
+            }
+        wave_lds_fence();
+    };
+    auto flush = [&]() __attribute__((always_inline)) {
+        wave_lds_fence();
         for (int k = lane; k < cnt; k += SYM_RUN) {
             const int jg = s_idx[k];
             const bool in = jg < n;
@@ -1473,52 +1536,44 @@ k_sym_fold_near(const float* __restrict__ jpart, const float4* __restrict__ pos,
                 s_x64[3 * k + 2] = in ? x64[3 * (size_t)jg + 2] : 0.0;
             }
         }
-        __syncthreads();
-        // the FP32 test for groups of 8 candidates, then the pairs it found
-        // in ascending order
-        for (int e0 = 0; e0 < cnt; e0 += 8) {
-            uint32_t nm = 0;
+        wave_lds_fence();
+        // the FP32 test for groups of 8 candidates, and a list of the pairs that
+        // it found, one of every lane at a time
+        int np = 0, e0 = 0;      // e0: the next group
+        uint32_t nm = 0;         // this lane's pairs of the group before
+        for (;;) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(nm != 0u);
+            if (m == 0 && e0 < cnt) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (e0 + u < cnt) {
-                    const float4 pj = s_pos[e0 + u];
-                    const float dx = pdiff<PER>(xq, pj.x);
-                    const float dy = pdiff<PER>(yq, pj.y);
-                    const float dz = pdiff<PER>(zq, pj.z);
-                    if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < thr2) nm |= 1u << u;
-                }
-            }
-            for (; nm != 0u; nm &= nm - 1u) {
-                const int e = e0 + __builtin_ctz(nm);
-                const float4 pj = s_pos[e];
-                const int jg = s_idx[e];
-                if (jg != q && q < n && jg < n) {
-                    const float4 fj = s_frc[e];
-                    double d0, d1, d2;
-                    if (x64) {   // the FP64 positions, staged
-                        d0 = xq64[0] - s_x64[3 * e];
-                        d1 = xq64[1] - s_x64[3 * e + 1];
-                        d2 = xq64[2] - s_x64[3 * e + 2];
-                        if (PER) nearest_image_d(pc, d0, d1, d2);
-                    } else {
-                        near_diff_v<PER>(xq, yq, zq, q, pj, jg, pc, nullptr, d0, d1, d2);
-                    }
-                    const int cls = near_term<TENSOR>(pc, d0, d1, d2, (double)fj.x, (double)fj.y,
-                                                      (double)fj.z, v0, v1, v2);
-                    if (q < jg) {
-                        psub += cls == PREMISE_SUB2A;
-                        pco += cls == PREMISE_COINCIDENT;
+                for (int u = 0; u < 8; ++u) {
+                    if (e0 + u < cnt) {
+                        const float4 pj = s_pos[e0 + u];
+                        const int jg = s_idx[e0 + u];
+                        const float dx = pdiff<PER>(xq, pj.x);
+                        const float dy = pdiff<PER>(yq, pj.y);
+                        const float dz = pdiff<PER>(zq, pj.z);
+                        if (fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < thr2 && jg != q && q < n &&
+                            jg < n)
+                            nm |= 1u << u;
                     }
                 }
+                e0 += 8;
+                continue;
             }
+            const int add = __builtin_popcountll(m);
+            if (m == 0 || np + add > SYM_RUN) {
+                if (np > 0) pair_terms(np);
+                np = 0;
+                if (m == 0) break;
+            }
+            if (nm != 0u)
+                s_pair[np + __builtin_popcountll(m & ((1ull << lane) - 1ull))] =
+                    (uint16_t)(lane | (e0 - 8 + __builtin_ctz(nm)) << 8);
+            np += add;
+            nm &= nm - 1u;
         }
-        __syncthreads();
+        wave_lds_fence();
         cnt = 0;
-    };
-    auto add_range = [&](int j0, int len) {   // particles j0 .. j0 + len - 1, len <= 64
-        if (cnt + len > FOLD_CAP) flush();
-        if (lane < len) s_idx[cnt + lane] = j0 + lane;
-        cnt += len;
     };
     const int RB = B / SYM_RUN;          // runs (= flag rows) per block
     const int r = S - J * RB;            // q's run within its block
@@ -1529,75 +1584,108 @@ k_sym_fold_near(const float* __restrict__ jpart, const float4* __restrict__ pos,
     const int TB = B / SYM_TJ;           // tiles per block
     const uint4* ftile = (const uint4*)flags;
     const uint4* fdiag = ftile + rows * (size_t)nt;
-    for (uint32_t ch = fdiag[J * RB + w].z; ch != 0u; ch &= ch - 1u)
-        add_range(J * B + 16 * __builtin_ctz(ch), 16);
     const int ntJ = (sh.h + ((sh.extra && J < half) ? 1 : 0)) * TB;
     const uint4* frow = ftile + (size_t)(J * RB + w) * nt;
-    // (the entries are read by all lanes at once and handed out with readlane:
-    // a load per flagged entry would put a memory latency in the chain)
-    for (int t0 = 0; t0 < ntJ; t0 += 64) {
-        const uint32_t chl = t0 + lane < ntJ ? frow[t0 + lane].z : 0u;
-        uint64_t m = __builtin_amdgcn_ballot_w64(chl != 0u);
-        while (m) {
-            const int k = __builtin_ctzll(m);
-            m &= m - 1;
-            const int pt = (t0 + k) * SYM_TJ;
-            const int jt = ((J + 1 + pt / B) % nb) * B + pt % B;
-            for (uint32_t ch = __builtin_amdgcn_readlane(chl, k); ch != 0u; ch &= ch - 1u)
-                add_range(jt + 16 * __builtin_ctz(ch), 16);
-        }
-    }
     // q's block J is block d of the virtual range of I = J - d (d = 1 .. h),
     // and block h + 1 of I = J + nb / 2 when nb is even and I < nb / 2; q's
     // run covers chunks c0 .. c0 + 3 of its tile tq
     const int tq = (r * SYM_RUN) / SYM_TJ;
     const uint32_t rch = 0xFu << (((r * SYM_RUN) % SYM_TJ) / 16);
     const int Ie = (J + half) % nb;
-    const int dmax = sh.h + ((sh.extra && Ie < half) ? 1 : 0);
-    for (int c0 = 0; c0 < dmax * wpb; c0 += 64) {
-        uint4 ev = make_uint4(0u, 0u, 0u, 0u);
-        const int c = c0 + lane;          // c = (d - 1) wpb + w'
-        if (c < dmax * wpb) {
-            const int d = c / wpb + 1, wp = c % wpb;
-            const int I = (J - d + nb) % nb;
-            ev = ftile[(size_t)(I * RB + wp) * nt + (size_t)((d - 1) * TB + tq)];
+    const int ne = (sh.h + ((sh.extra && Ie < half) ? 1 : 0)) * wpb;
+    // The sources one after the other: 0 the diagonal block (wave 0), 1 the row of
+    // q's wave, 2 the preceding blocks.  64 entries of 1 or 2 are read at a time,
+    // one by every lane, and handed out with readlane (a load per flagged entry
+    // would put a memory latency in the chain).
+    int source = wv == 0 ? 0 : 1, next = wv, cur = 0;   // next entry, first of the 64 held
+    uint64_t m = 0;                                     // flagged entries of the 64
+    uint32_t ch = 0;                                    // flagged chunks of an entry ...
+    int jt = 0;                                         // ... whose tile starts here
+    uint4 ev = make_uint4(0u, 0u, 0u, 0u);
+    for (;;) {
+        uint64_t lanes = 0;   // lanes with a candidate, ncand of them, in steps of jstep
+        int j = 0, ncand = 1, jstep = 0;
+        for (;;) {
+            if (ch != 0u) {
+                lanes = 0xffffull;
+                j = jt + 16 * __builtin_ctz(ch) + lane;
+                ch &= ch - 1u;
+                break;
+            }
+            if (m != 0) {
+                const int k = __builtin_ctzll(m), e = cur + NW * k;
+                m &= m - 1;
+                if (source == 1) {
+                    const int pt = e * SYM_TJ;
+                    jt = ((J + 1 + pt / B) % nb) * B + pt % B;
+                    ch = __builtin_amdgcn_readlane(ev.z, k);
+                    continue;
+                }
+                // lane k of wave w' holds particles I B + l BLOCK + 64 w' + k
+                const int d = e / wpb + 1, wp = e % wpb;
+                const int I = (J - d + nb) % nb;
+                lanes = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(ev.y, k) << 32) |
+                        (uint32_t)__builtin_amdgcn_readlane(ev.x, k);
+                j = I * B + wp * SYM_RUN + lane;
+                ncand = ilp;
+                jstep = wpb * SYM_RUN;
+                break;
+            }
+            if (source == 0) {
+                ch = fdiag[J * RB + w].z;
+                jt = J * B;
+                source = 1;
+                continue;
+            }
+            if (next < (source == 1 ? ntJ : ne)) {
+                const int e = next + NW * lane;   // source 2: e = (d - 1) wpb + w'
+                ev = make_uint4(0u, 0u, 0u, 0u);
+                if (source == 1) {
+                    if (e < ntJ) ev.z = frow[e].z;
+                    m = __builtin_amdgcn_ballot_w64(ev.z != 0u);
+                } else {
+                    if (e < ne) {
+                        const int d = e / wpb + 1, wp = e % wpb;
+                        const int I = (J - d + nb) % nb;
+                        ev = ftile[(size_t)(I * RB + wp) * nt + (size_t)((d - 1) * TB + tq)];
+                    }
+                    m = __builtin_amdgcn_ballot_w64((ev.z & rch) != 0u);
+                }
+                cur = next;
+                next += 64 * NW;
+                continue;
+            }
+            if (source == 2) break;   // no more
+            source = 2;
+            next = wv;
         }
-        uint64_t m = __builtin_amdgcn_ballot_w64((ev.z & rch) != 0u);
-        while (m) {
-            const int k = __builtin_ctzll(m);
-            m &= m - 1;
-            const int cc = c0 + k;
-            const int d = cc / wpb + 1, wp = cc % wpb;
-            const int I = (J - d + nb) % nb;
-            const uint64_t lanes = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(ev.y, k) << 32) |
-                                   (uint32_t)__builtin_amdgcn_readlane(ev.x, k);
-            // lane k of wave w' holds particles I B + l BLOCK + 64 w' + k
-            const int add = __builtin_popcountll(lanes) * ilp;
-            if (cnt + add > FOLD_CAP) flush();
-            const int at = __builtin_popcountll(lanes & ((1ull << lane) - 1ull));
-            if ((lanes >> lane) & 1)
-                for (int l = 0; l < ilp; ++l)
-                    s_idx[cnt + at * ilp + l] = I * B + l * (wpb * SYM_RUN) + wp * SYM_RUN + lane;
-            cnt += add;
+        const int add = __builtin_popcountll(lanes) * ncand;
+        if (add == 0 || cnt + add > FOLD_CAP) {
+            if (cnt > 0) flush();
+            if (add == 0) break;
         }
+        const int at = cnt + __builtin_popcountll(lanes & ((1ull << lane) - 1ull)) * ncand;
+        if ((lanes >> lane) & 1)
+            for (int l = 0; l < ncand; ++l) s_idx[at + l] = j + l * jstep;
+        cnt += add;
     }
-    if (cnt > 0) flush();
     count_premise_lanes(psub, pco);
-    if (q < n) {
-        if (vel) {
-            // the merge: mu0 F + rows 0 .. isplits in order + this row (k_merge's sum)
-            const float4 fq = frc[q];
-            double w0 = mu0 * (double)fq.x, w1 = mu0 * (double)fq.y, w2 = mu0 * (double)fq.z;
-            add_split_rows(partial, sh.isplits + 1, n, q, w0, w1, w2);
-            vel[3 * (size_t)q + 0] = w0 + v0;
-            vel[3 * (size_t)q + 1] = w1 + v1;
-            vel[3 * (size_t)q + 2] = w2 + v2;
-        } else {
-            out[q] = v0;
-            out[(size_t)n + q] = v1;
-            out[2 * (size_t)n + q] = v2;
-        }
+    s_sum[wv][0][lane] = v0;
+    s_sum[wv][1][lane] = v1;
+    s_sum[wv][2][lane] = v2;
+    __syncthreads();
+    if (wv != 0 || q >= n) return;
+    const float4 fq = frc[q];
+    double u[3] = { pc.mu0 * (double)fq.x, pc.mu0 * (double)fq.y, pc.mu0 * (double)fq.z };
+    for (int k = 0; k < NW; ++k)
+        for (int c = 0; c < 3; ++c) u[c] += s_sum[k][c][lane];
+    if (vel) {
+        for (int c = 0; c < 3; ++c) vel[3 * (size_t)q + c] = u[c];
+        return;
     }
+    double xn[3];
+    step_particle(st, q, u, xn);
+    if (pos_next) put_pos(pos_next, q, xn[0], xn[1], xn[2], qs);
 }
 
 // ---------------------------------------------------------------- FP64 path
@@ -1758,20 +1846,19 @@ static hipError_t launch_f32_sym(const PairLaunch& L, const float4* pos, const f
 }
 
 hipError_t launch_pair_fold(const PairLaunch& L, int tensor, const float4* pos, const float4* frc,
-                            const double* x64, int n, const PairConst& pc, double* partial,
-                            hipStream_t st, double mu0, double* vel)
+                            const double* x64, int n, const PairConst& pc, const double* partial,
+                            double* vel, const StepOut& step, void* pos_next, hipStream_t st)
 {
-    if (L.variant != 2) return hipSuccess;
     const SymShape sh = sym_shape_of(L, n);
     const float* jpart = (const float*)((const char*)partial + sym_jpart_offset(L, n));
-    uint8_t* flags = (uint8_t*)partial + sym_flags_offset(L, n);
-    double* out = partial + (size_t)(sh.isplits + 1) * 3 * (size_t)n;
+    const uint8_t* flags = (const uint8_t*)partial + sym_flags_offset(L, n);
     const int B = L.block * L.ilp;
     const bool per = pc.box > 0.0;
+    const double qs = per ? 4294967296.0 / pc.box : 0.0;
 #define SD_FOLD(T, P)                                                                      \
-    hipLaunchKernelGGL((k_sym_fold_near<T, P>), dim3(sh.nb * (B / SYM_RUN)), dim3(SYM_RUN), 0, \
-                       st, jpart, pos, frc, x64, n, B, L.block / 64, sh, pc, flags, out,   \
-                       partial, mu0, vel)
+    hipLaunchKernelGGL((k_sym_fold_near<T, P>), dim3(sh.nb * (B / SYM_RUN)),               \
+                       dim3(4 * SYM_RUN), 0, st, jpart, pos, frc, x64, n, B, L.block / 64, \
+                       sh, pc, flags, partial, vel, step, (float4*)pos_next, qs)
     if (tensor == T_OSEEN) {
         if (per) SD_FOLD(T_OSEEN, true); else SD_FOLD(T_OSEEN, false);
     } else {

@@ -136,4 +136,19 @@ __device__ __forceinline__ void put_pos(double4* p, int i, double a, double b, d
     p[i] = make_double4(a, b, c, 0.0);
 }
 
+// The step of particle i with velocity v (see StepOut); xn: its new position.
+__device__ __forceinline__ void step_particle(const StepOut& o, int i, const double (&v)[3],
+                                              double (&xn)[3])
+{
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const size_t e = 3 * (size_t)i + c;
+        const double inc = (o.mode == 2) ? (1.5 * v[c] - 0.5 * o.v_prev[e]) : v[c];
+        xn[c] = o.x_in[e] + o.dt * inc;
+        o.x_out[e] = xn[c];
+        if (o.mode != 0) o.v_prev[e] = v[c];
+        if (o.v_out) o.v_out[e] = v[c];
+    }
+}
+
 }  // namespace sd

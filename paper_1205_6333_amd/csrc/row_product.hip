@@ -37,14 +37,7 @@ __device__ __forceinline__ void row_finish(const RowOut& o, int i, const V4 f, c
         return;
     }
     double xn[3];
-    for (int c = 0; c < 3; ++c) {
-        const size_t e = 3 * (size_t)i + c;
-        const double inc = (o.mode == 2) ? (1.5 * v[c] - 0.5 * o.v_prev[e]) : v[c];
-        xn[c] = o.x_in[e] + o.dt * inc;
-        o.x_out[e] = xn[c];
-        if (o.mode != 0) o.v_prev[e] = v[c];
-        if (o.v_out) o.v_out[e] = v[c];
-    }
+    step_particle({ o.x_in, o.x_out, o.v_prev, o.v_out, o.dt, o.mode }, i, v, xn);
     if (o.pos_next) put_pos((V4*)o.pos_next, i, xn[0], xn[1], xn[2], o.qs);
 }
 

@@ -409,12 +409,10 @@ sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* f
     if (e == hipSuccess && L.variant == 3 && vel)
         e = launch_wave_fold(L, prec == SD_FP64, (int)n, pc, partial, frc, vel, nullptr, nullptr,
                              nullptr, nullptr, 0.0, 0, nullptr, st);
-    const bool fuse = vel && (L.variant == 2 || L.variant == 3);
-    if (e == hipSuccess && prec != SD_FP64)
+    if (e == hipSuccess && L.variant == 2 && vel)
         e = launch_pair_fold(L, p->tensor, (const float4*)pos, (const float4*)frc, x64, (int)n, pc,
-                             partial, st, 1.0 / (6.0 * M_PI * p->eta * p->a),
-                             vel);
-    if (e == hipSuccess && fuse && merged) *merged = true;
+                             partial, vel, StepOut{}, nullptr, st);
+    if (e == hipSuccess && vel && (L.variant == 2 || L.variant == 3) && merged) *merged = true;
     if (e != hipSuccess) return fail(SD_EDEVICE, "pair kernel launch: %s", hipGetErrorString(e));
     return SD_OK;
 }
@@ -437,7 +435,11 @@ sd_status run_step(const sd_params* p, int64_t n, const double* x_in, double* x_
     }
     sd_status r = run_pair(p, n, pos, frc, f64 ? nullptr : x_in, prec, partial, L, st);
     if (r) return r;
-    if (L.variant == 3)
+    if (L.variant == 2)
+        e = launch_pair_fold(L, p->tensor, (const float4*)pos, (const float4*)frc, x_in, (int)n,
+                             pair_const(p), partial, nullptr,
+                             StepOut{ x_in, x_out, v_prev, v_out, dt, mode }, pos_next, st);
+    else if (L.variant == 3)
         e = launch_wave_fold(L, f64, (int)n, pair_const(p), partial, frc, nullptr, x_in, x_out,
                              v_prev, v_out, dt, mode, pos_next, st);
     else
@@ -456,11 +458,12 @@ sd_status step_buffers(const PairLaunch& L, int64_t n, int32_t prec, StepBuffers
     if ((st = ws_get(WS_PARTIAL, partial_bytes(L, n), &partial)) ||
         (st = ws_get(WS_STAGE, 2 * rec, &stage)))
         return st;
-    if (L.variant == 4 && (st = ws_get(WS_STEP_X, 3 * (size_t)n * sizeof(double), &copy)))
+    const bool apart = step_apart(L);
+    if (apart && (st = ws_get(WS_STEP_X, 3 * (size_t)n * sizeof(double), &copy)))
         return st;
     sb->partial = (double*)partial;
     sb->pos[0] = (char*)stage;
-    sb->pos[1] = L.variant == 4 ? (char*)stage + rec : (char*)stage;
+    sb->pos[1] = apart ? (char*)stage + rec : (char*)stage;
     sb->copy = (double*)copy;
     return SD_OK;
 }
@@ -468,12 +471,12 @@ sd_status step_buffers(const PairLaunch& L, int64_t n, int32_t prec, StepBuffers
 sd_status steps_begin(const sd_params* p, int64_t n, double* x, int64_t steps, int32_t prec,
                       const PairLaunch& L, StepBuffers* sb, hipStream_t st)
 {
-    const bool odd = L.variant == 4 && (steps & 1);
+    const bool odd = step_apart(L) && (steps & 1);
     const hipError_t e = launch_stage(prec == SD_FP64, x, sb->pos[0], (int)n, box_side(p),
                                       odd ? sb->copy : nullptr, st);
     if (e != hipSuccess) return fail(SD_EDEVICE, "stage launch: %s", hipGetErrorString(e));
     sb->cur = odd ? sb->copy : x;
-    sb->other = L.variant == 4 && !odd ? sb->copy : x;
+    sb->other = step_apart(L) && !odd ? sb->copy : x;
     return SD_OK;
 }
 

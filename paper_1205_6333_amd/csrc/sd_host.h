@@ -88,9 +88,11 @@ sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* f
                    const double* x64, int32_t prec, double* partial, const PairLaunch& L,
                    hipStream_t st, double* vel = nullptr, bool* merged = nullptr);
 
+// The last kernel of a step reads the positions of other particles than it writes.
+inline bool step_apart(const PairLaunch& L) { return L.variant == 2 || L.variant == 4; }
 // One time step from x_in to x_out (mode as launch_merge_integrate).  pos: the
 // records of x_in; pos_next (may be null) receives those of x_out.  x_out may
-// be x_in and pos_next may be pos unless the launch is of variant 4.
+// be x_in and pos_next may be pos unless step_apart(L).
 sd_status run_step(const sd_params* p, int64_t n, const double* x_in, double* x_out,
                    const void* frc, double* v_prev, double* v_out, double dt, int mode,
                    int32_t prec, const void* pos, void* pos_next, double* partial,

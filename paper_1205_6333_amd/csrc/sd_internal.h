@@ -88,8 +88,8 @@ PairLaunch shape_pair_launch(int n, int variant, int block, int splits, int ilp,
 // tiles) is cut into isplits splits, split k covering tiles
 // [off[k], off[k+1]).  The splits shrink towards the end (see sym_shape), so
 // that the last work-groups of a launch are short.  Partial rows: isplits
-// symmetric splits, one row of the one-sided diagonal blocks, one row of the
-// folded j side and the near pairs, so PairLaunch.splits = isplits + 2.
+// symmetric splits and one row of the one-sided diagonal blocks, so
+// PairLaunch.splits = isplits + 1.
 // After the rows (256-byte aligned) the workspace holds the FP32 j-side
 // partials, 3 * nb * lmax floats, then (256-byte aligned) the near-pair
 // records: one 16-byte entry per wave row and tile of the virtual range, then
@@ -127,16 +127,26 @@ hipError_t launch_pair_f32(const PairLaunch& L, int tensor, int acc, const float
                            double* partial, hipStream_t st);
 hipError_t launch_pair_f64(const PairLaunch& L, int tensor, const double4* pos, const double4* frc,
                            int n, const PairConst& pc, double* partial, hipStream_t st);
-// Variant 2 only (a no-op otherwise): the last partial row, from the j-side
-// partials and the near-pair flags the pair kernel left in the workspace.
-// pos/frc: the records the pair kernel read; x64 as for launch_pair_f32.
-// Enqueue after the pair kernel, before anything reads the partial rows.
-// With vel (f64[3n]) given, the fold also does the merge: vel = mu0 F + the
-// split rows in order + the folded row, the sum k_merge forms, bit for bit,
-// and the folded row is not written.
+// A time step of the positions: x_out = x_in + dt (the integrator's velocity),
+// mode 0 Euler, 1 AB2 start (v_prev written), 2 AB2 (v_prev read and written);
+// v_out (may be null) receives the velocities.
+struct StepOut {
+    const double* x_in;
+    double* x_out;
+    double* v_prev;
+    double* v_out;
+    double dt;
+    int mode;
+};
+// Variant 2: the end of a product (vel given) or of a time step (vel null), from
+// the split rows, the j-side partials and the near-pair flags that the pair
+// kernel left in the workspace.  pos/frc: the records the pair kernel read; x64
+// as for launch_pair_f32.  Other work-groups read the particles near theirs:
+// step.x_out is another array than x64, and pos_next (may be null) other records
+// than pos.
 hipError_t launch_pair_fold(const PairLaunch& L, int tensor, const float4* pos, const float4* frc,
-                            const double* x64, int n, const PairConst& pc, double* partial,
-                            hipStream_t st, double mu0 = 0.0, double* vel = nullptr);
+                            const double* x64, int n, const PairConst& pc, const double* partial,
+                            double* vel, const StepOut& step, void* pos_next, hipStream_t st);
 
 // Variant 3 (wave_sym.h): the pair kernels (x64 as for launch_pair_f32; both
 // with two particles per lane), and the fold that adds their partials and writes

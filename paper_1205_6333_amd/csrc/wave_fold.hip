@@ -81,14 +81,7 @@ k_wave_fold(const double* __restrict__ partial, const double* __restrict__ jpart
         return;
     }
     double xn[3];
-    for (int c = 0; c < 3; ++c) {
-        const size_t e = 3 * (size_t)i + c;
-        const double inc = (mode == 2) ? (1.5 * u[c] - 0.5 * v_prev[e]) : u[c];
-        xn[c] = x_in[e] + dt * inc;
-        x_out[e] = xn[c];
-        if (mode != 0) v_prev[e] = u[c];
-        if (v_out) v_out[e] = u[c];
-    }
+    step_particle({ x_in, x_out, v_prev, v_out, dt, mode }, i, u, xn);
     if (pos_next) put_pos(pos_next, i, xn[0], xn[1], xn[2], qs);
 }
 
