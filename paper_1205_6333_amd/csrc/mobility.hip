@@ -156,9 +156,9 @@ __device__ __forceinline__ void near_diff(const LaneF32& L, const float4 pj, int
 }
 
 // Unordered pairs i < j met by the product kernels on this device that break
-// the premise r >= 2a of Eq. 4: [0] with 0 < r < 2a, [1] with r = 0.  Counted
+// the premise r >= 2a of Eq. 4 (see premise.h).  Counted
 // on the rare FP64 near-pair branch only, by the evaluation of row min(i, j).
-__device__ unsigned long long g_premise[2];
+__device__ unsigned long long g_premise[PREMISE_SLOTS * PREMISE_STRIDE];
 
 __device__ __forceinline__ void count_premise(int cls) { count_premise(g_premise, cls); }
 
@@ -170,10 +170,7 @@ __device__ __forceinline__ void count_premise_lanes(uint32_t sub, uint32_t co)
         sub += __shfl_xor(sub, off);
         co += __shfl_xor(co, off);
     }
-    if ((threadIdx.x & 63) == 0) {
-        if (sub) atomicAdd(&g_premise[0], (unsigned long long)sub);
-        if (co) atomicAdd(&g_premise[1], (unsigned long long)co);
-    }
+    if ((threadIdx.x & 63) == 0) add_premise(g_premise, sub, co);
 }
 
 // One pair (i, j) on the FP32 fast path.  pj/fj: position and force of j
@@ -1950,7 +1947,7 @@ hipError_t launch_pair_f64(const PairLaunch& L, int tensor, const double4* pos, 
 
 __global__ void k_premise_clear(unsigned long long* c)
 {
-    if (threadIdx.x < 2) c[threadIdx.x] = 0ull;
+    for (int k = threadIdx.x; k < PREMISE_SLOTS * PREMISE_STRIDE; k += 64) c[k] = 0ull;
 }
 
 hipError_t premise_counters(unsigned long long** counters)
@@ -1964,13 +1961,15 @@ hipError_t premise_counts(int64_t* sub2a, int64_t* coincident, bool reset, hipSt
     unsigned long long* dev = nullptr;
     hipError_t e = premise_counters(&dev);
     if (e != hipSuccess) return e;
-    unsigned long long h[2] = { 0ull, 0ull };
+    unsigned long long h[PREMISE_SLOTS * PREMISE_STRIDE];
     if ((e = hipMemcpyAsync(h, dev, sizeof h, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
     if (reset) {
         hipLaunchKernelGGL(k_premise_clear, dim3(1), dim3(64), 0, st, dev);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    for (int s = 1; s < PREMISE_SLOTS; ++s)
+        for (int c = 0; c < 2; ++c) h[c] += h[s * PREMISE_STRIDE + c];
     if (sub2a) *sub2a = (int64_t)h[0];
     if (coincident) *coincident = (int64_t)h[1];
     return hipSuccess;

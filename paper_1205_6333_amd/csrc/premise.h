@@ -6,14 +6,26 @@
 
 namespace sd {
 
-// The current device's counters, [0] pairs with 0 < r < 2a, [1] with r = 0
-// (defined beside the product kernels in mobility.hip).
+// The current device's counters (defined beside the product kernels in
+// mobility.hip): PREMISE_SLOTS cache lines of [0] pairs with 0 < r < 2a and [1]
+// with r = 0, to be added up.  Work-groups take the slots in turn, since atomics
+// on one address serialise: microseconds with one slot -> this: products of N =
+// 3000 with 0.6 near partners per particle 18.6 -> 14.9 (5000 30.5 -> 27.8), the
+// fold of N = 65536 with 0.4 85 -> 73.
+constexpr int PREMISE_SLOTS = 256, PREMISE_STRIDE = 8;
 hipError_t premise_counters(unsigned long long** counters);
+
+__device__ __forceinline__ void add_premise(unsigned long long* counters, uint32_t sub,
+                                            uint32_t co)
+{
+    unsigned long long* const c = counters + (blockIdx.x % PREMISE_SLOTS) * PREMISE_STRIDE;
+    if (sub) atomicAdd(&c[0], (unsigned long long)sub);
+    if (co) atomicAdd(&c[1], (unsigned long long)co);
+}
 
 // Called by the lanes active at that point, each with the class of its pair
 // (PREMISE_OK for none): one atomic add per class and call, by one lane, for
-// the whole wave (a dense suspension meets thousands of such pairs per
-// product, and atomics on one address serialise).
+// the whole wave.
 __device__ __forceinline__ void count_premise(unsigned long long* counters, int cls)
 {
     const uint64_t sub = __builtin_amdgcn_ballot_w64(cls == PREMISE_SUB2A);
@@ -21,8 +33,7 @@ __device__ __forceinline__ void count_premise(unsigned long long* counters, int 
     if ((sub | co) == 0) return;
     const uint64_t act = __builtin_amdgcn_ballot_w64(true);
     if ((int)(threadIdx.x & 63) != __builtin_ctzll(act)) return;
-    if (sub) atomicAdd(&counters[0], (unsigned long long)__builtin_popcountll(sub));
-    if (co) atomicAdd(&counters[1], (unsigned long long)__builtin_popcountll(co));
+    add_premise(counters, __builtin_popcountll(sub), __builtin_popcountll(co));
 }
 
 }  // namespace sd
