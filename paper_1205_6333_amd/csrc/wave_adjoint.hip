@@ -81,8 +81,9 @@ __device__ __forceinline__ AdjCoef<double> adj_near_coef(const PairConst& pc, do
 }
 
 // One pair: G to g and cg, T lam_j to m, T lam_i to cm (the terms of j; first:
-// cg and cm are started; start: g and m are started).
-template <typename T>
+// cg and cm are started; start: g and m are started).  FINE: G is rounded into g
+// without a rounding of its own.
+template <typename T, bool FINE = false>
 __device__ __forceinline__ void adj_pair(const AdjCoef<T>& c, const V3<T>& d, const V3<T>& fi,
                                          const V3<T>& li, const V3<T>& fj, const V3<T>& lj,
                                          V3<T>& g, V3<T>& m, V3<T>& cg, V3<T>& cm, bool first,
@@ -95,8 +96,11 @@ __device__ __forceinline__ void adj_pair(const AdjCoef<T>& c, const V3<T>& d, co
     const T bli = c.Bt * li_d, bfj = c.Bt * fj_d, blj = c.Bt * lj_d, bfi = c.Bt * fi_d;
 #define SD_COMP(k)                                                                              \
     do {                                                                                        \
-        const T G = fma(c1, d.k, fma(bfj, li.k, fma(bli, fj.k, fma(bfi, lj.k, blj * fi.k))));   \
-        g.k = start ? G : g.k + G;                                                              \
+        const T W = fma(fj_d, li.k, fma(li_d, fj.k, fma(fi_d, lj.k, lj_d * fi.k)));             \
+        const T G = FINE ? fma(c1, d.k, c.Bt * W)                                               \
+                         : fma(c1, d.k, fma(bfj, li.k, fma(bli, fj.k, fma(bfi, lj.k, blj * fi.k)))); \
+        if (FINE) g.k = fma(c1, d.k, fma(c.Bt, W, g.k));                                        \
+        else g.k = start ? G : g.k + G;                                                         \
         m.k = fma(c.A, lj.k, start ? blj * d.k : fma(blj, d.k, m.k));                           \
         cg.k = first ? G : cg.k + G;                                                            \
         cm.k = fma(c.A, li.k, first ? bli * d.k : fma(bli, d.k, cm.k));                         \
@@ -124,8 +128,10 @@ __device__ __forceinline__ void adj_pair(const AdjCoef<T>& c, const V3<T>& d, co
 // faster in FP32 at N = 8192 and 7 % slower there at N = 3001.  Microseconds
 // per pass with the fold (one-sided kernel and merge): FP64 N = 3001 29 (134),
 // FP32 N = 8192 86 (131).
-template <int TENSOR, typename T>
-__global__ void __launch_bounds__(256, 3)
+// FINE (FP32, small n): the i side compensated with every term, the j side in
+// blocks of two.
+template <int TENSOR, typename T, bool FINE>
+__global__ void __launch_bounds__(256, FINE ? 2 : 3)
 k_wave_adjoint(const typename Vec4<T>::type* __restrict__ pos,
                const typename Vec4<T>::type* __restrict__ frc,
                const typename Vec4<T>::type* __restrict__ lam, const double* __restrict__ x64,
@@ -135,8 +141,9 @@ k_wave_adjoint(const typename Vec4<T>::type* __restrict__ pos,
     typedef typename Vec4<T>::type V4;
     constexpr bool F32 = sizeof(T) == 4;
     constexpr int ILP = 1, B = 64 * ILP;
-    constexpr int IB = 2, IK = 4, JB = 4;   // FP32 summation blocks
-    constexpr int JH = F32 ? 2 : 1;         // j-side sums per chunk, row and element
+    // FP32 summation blocks
+    constexpr int IB = 2, IK = 4, JB = FINE ? 1 : 4;
+    constexpr int JH = F32 ? 8 / JB : 1;    // j-side sums per chunk, row and element
     constexpr int RS = F32 ? 12 : 10;   // values per staged record (16-byte multiples)
     __shared__ __align__(16) T s_rec[4][32 * RS];
     __shared__ T s_j[4][4 * JH * 96];
@@ -265,8 +272,16 @@ k_wave_adjoint(const typename Vec4<T>::type* __restrict__ pos,
                     rinv = rsqrt_f64(r2[a]);
                 }
                 const AdjCoef<T> co = adj_far<TENSOR, T>(rinv, gamma, g3, g15);
-                adj_pair<T>(co, d[a], f[a], l[a], fj, lj, g[a], m[a], cg, cm, a == 0,
-                            F32 && k % IB == 0);
+                if constexpr (FINE) {   // compensated with every term
+                    g[a] = gc[a];
+                    m[a] = mc[a];
+                }
+                adj_pair<T, FINE>(co, d[a], f[a], l[a], fj, lj, g[a], m[a], cg, cm, a == 0,
+                                  F32 && !FINE && k % IB == 0);
+                if constexpr (FINE) {
+                    kahan(gs[a], gc[a], g[a]);
+                    kahan(ms[a], mc[a], m[a]);
+                }
             }
             // hand-over to the owner of the element; FP32: JB steps, then the sum
             if constexpr (F32 && k % JB == 0) {
@@ -296,7 +311,7 @@ k_wave_adjoint(const typename Vec4<T>::type* __restrict__ pos,
             }
             // FP32, i side: blocks of IB terms into the running sum, compensated
             // once per IK terms
-            if constexpr (F32 && k % IB == IB - 1) {
+            if constexpr (F32 && !FINE && k % IB == IB - 1) {
 #pragma unroll
                 for (int a = 0; a < ILP; ++a) {
                     yg[a] = add(k % IK == IB - 1 ? gc[a] : yg[a], g[a]);
@@ -520,6 +535,13 @@ size_t wave_adjoint_bytes(const PairLaunch& L, int64_t n)
     return 2 * (wave_jpart_offset(sh, n) + wave_jpart_bytes(sh, sizeof(double)));
 }
 
+// FP32 passes below this size compensate with every term.  The one-sided kernel
+// cut a short row into many FP64 parts, and in blocks the error of M lam was 1.2
+// times its at N = 20 (48 1.1, 120 1.1, 700 and above 1.0); with every term 1.0, 1.0,
+// 0.95.  Microseconds, blocks / every term: N = 300 11.4 / 12.1, 1000 12.0 / 12.5,
+// 1500 13.3 / 15.0, 3000 23.4 / 30.0.
+constexpr int FINE_END_N = 1024;
+
 template <int TENSOR, typename T>
 static hipError_t launch_t(const PairLaunch& L, const void* pos, const void* frc, void* lam,
                            const double* x64, int n, const PairConst& pc, void* ws, double* lam64,
@@ -529,9 +551,15 @@ static hipError_t launch_t(const PairLaunch& L, const void* pos, const void* frc
     const WaveShape sh = wave_shape_of(L, n);
     double* partial = (double*)ws;
     double* jpart = (double*)((char*)ws + 2 * wave_jpart_offset(sh, n));
-    hipLaunchKernelGGL((k_wave_adjoint<TENSOR, T>), dim3((unsigned)(sh.nb * (sh.splits + 1))),
-                       dim3(256), 0, st, (const V4*)pos, (const V4*)frc, (const V4*)lam, x64, n, sh,
-                       pc, partial, jpart);
+    const dim3 grid((unsigned)(sh.nb * (sh.splits + 1)));
+    if (sizeof(T) == 4 && n < FINE_END_N)
+        hipLaunchKernelGGL((k_wave_adjoint<TENSOR, T, sizeof(T) == 4>), grid, dim3(256), 0, st,
+                           (const V4*)pos, (const V4*)frc, (const V4*)lam, x64, n, sh, pc,
+                           partial, jpart);
+    else
+        hipLaunchKernelGGL((k_wave_adjoint<TENSOR, T, false>), grid, dim3(256), 0, st,
+                           (const V4*)pos, (const V4*)frc, (const V4*)lam, x64, n, sh, pc,
+                           partial, jpart);
     hipLaunchKernelGGL((k_wave_adjoint_fold<V4>), dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st,
                        partial, jpart, n, 64, sh, pc.alpha, (V4*)lam, lam64, pc.mu0, dt, gpos,
                        gforce);
