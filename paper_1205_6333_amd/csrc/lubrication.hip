@@ -17,6 +17,7 @@
 #include "sd.h"
 #include "sd_host.h"
 #include "sd_internal.h"
+#include "wave_sym.h"
 
 #include <algorithm>
 #include <cmath>
@@ -34,9 +35,21 @@ struct CellHash {
 };
 
 struct LubConst {
-    double a, mu0, s_cut, s_min, rcut2;
+    double a, imu0, s_cut, s_min, rcut2;
+    double ibox;     // 1 / box where the box is wider than two cutoffs, else 0
     PairConst pc;    // box for the nearest image
 };
+
+// Nearest image of a difference.  In a box wider than two cutoffs the product
+// with 1 / box rounds to another image than the quotient only for a pair about
+// half a box apart, which no image brings within the cutoff.
+__device__ __forceinline__ void lub_image(const LubConst& lc, double (&d)[3])
+{
+    if (lc.ibox > 0.0)
+        for (int k = 0; k < 3; ++k) d[k] -= lc.pc.box * rint(d[k] * lc.ibox);
+    else
+        nearest_image_d(lc.pc, d[0], d[1], d[2]);
+}
 
 __device__ __forceinline__ int cell_coord(const CellHash& g, double v)
 {
@@ -58,15 +71,15 @@ __device__ __forceinline__ unsigned bucket_of(const CellHash& g, int cx, int cy,
     return ((k ^ (k >> 16)) + (unsigned)cx) & g.mask;
 }
 
+// link[i]: the particle's cell, and the next particle of its bucket.
 __global__ void __launch_bounds__(256) k_lub_insert(const double* __restrict__ x, int n, CellHash g,
-                                                    int* __restrict__ head, int* __restrict__ next)
+                                                    int* __restrict__ head, int4* __restrict__ link)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    const unsigned b = bucket_of(g, cell_coord(g, x[3 * (size_t)i]),
-                                 cell_coord(g, x[3 * (size_t)i + 1]),
-                                 cell_coord(g, x[3 * (size_t)i + 2]));
-    next[i] = atomicExch(&head[b], i);
+    const int cx = cell_coord(g, x[3 * (size_t)i]), cy = cell_coord(g, x[3 * (size_t)i + 1]),
+              cz = cell_coord(g, x[3 * (size_t)i + 2]);
+    link[i] = make_int4(cx, cy, cz, atomicExch(&head[bucket_of(g, cx, cy, cz)], i));
 }
 
 // The m-th distinct neighbour (m = 0, 1, 2) of cell c along one axis: c - 1, c,
@@ -92,16 +105,20 @@ __device__ __forceinline__ bool axis_neighbour(const CellHash& g, int c, int m, 
 // chains are walked side by side: the kernel is bound by the latency of a chain
 // (bucket, particle, position).  A lane takes the close particles of its cell
 // LUB_TAKE at a time in ascending index; a cell with more is walked again.
-// Microseconds per lubrication_forces (three launches), where ten launches
-// (bounding box, grid, count, three scan passes, scatter, sort, forces with one
-// lane per particle) were used before: N = 100 60 -> 16, 5000 83 -> 16, 20000 82
-// -> 20, 65536 98 -> 45, 200000 156 -> 139.
+// A particle's cell is kept beside its link, so that a step of the chain tests three
+// integers before it loads a position (periodic fcc lattice of 202612, 12 close
+// particles each: 333 us with the cells computed anew and divisions for the image
+// and the unit vectors, 233 so).  Microseconds per lubrication_forces (three
+// launches), where ten launches (bounding box, grid, count, three scan passes,
+// scatter, sort, forces with one lane per particle) were used before: N = 100 60 ->
+// 12, 5000 83 -> 13, 20000 82 -> 18, 65536 98 -> 45, 200000 156 -> 139; the lattice 253
+// -> 233.
 constexpr int LUB_TAKE = 4;
 
 __global__ void __launch_bounds__(256)
 k_lub_force(const double* __restrict__ x, const double* __restrict__ v,
             const double* __restrict__ f_ext, int n, CellHash g, const int* __restrict__ head,
-            const int* __restrict__ next, LubConst lc, double* __restrict__ f_out,
+            const int4* __restrict__ link, LubConst lc, double* __restrict__ f_out,
             float4* __restrict__ rec32, double4* __restrict__ rec64)
 {
     const int i = blockIdx.x * 8 + (threadIdx.x >> 5);
@@ -111,9 +128,10 @@ k_lub_force(const double* __restrict__ x, const double* __restrict__ v,
     double acc[3] = { 0.0, 0.0, 0.0 };
     int cc[3];
     bool cell = q < 27;
-    cell = axis_neighbour(g, cell_coord(g, xi[0]), q % 3, cc[0]) && cell;
-    cell = axis_neighbour(g, cell_coord(g, xi[1]), q / 3 % 3, cc[1]) && cell;
-    cell = axis_neighbour(g, cell_coord(g, xi[2]), q / 9, cc[2]) && cell;
+    const int4 ci = link[i];
+    cell = axis_neighbour(g, ci.x, q % 3, cc[0]) && cell;
+    cell = axis_neighbour(g, ci.y, q / 3 % 3, cc[1]) && cell;
+    cell = axis_neighbour(g, ci.z, q / 9, cc[2]) && cell;
     if (cell) {
         const int first = head[bucket_of(g, cc[0], cc[1], cc[2])];
         int last = -1;
@@ -124,17 +142,17 @@ k_lub_force(const double* __restrict__ x, const double* __restrict__ v,
             int take[LUB_TAKE];
 #pragma unroll
             for (int k = 0; k < LUB_TAKE; ++k) take[k] = 0x7fffffff;
-            for (int j = first; j >= 0; j = next[j]) {
-                if (j == i || j <= last) continue;
+            int4 lj;
+            for (int j = first; j >= 0; j = lj.w) {
+                lj = link[j];
+                if (j == i || j <= last || lj.x != cc[0] || lj.y != cc[1] || lj.z != cc[2])
+                    continue;
                 const double xj[3] = { x[3 * (size_t)j], x[3 * (size_t)j + 1],
                                        x[3 * (size_t)j + 2] };
                 double d[3] = { xi[0] - xj[0], xi[1] - xj[1], xi[2] - xj[2] };
-                nearest_image_d(lc.pc, d[0], d[1], d[2]);
+                lub_image(lc, d);
                 const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
                 if (!(r2 < lc.rcut2) || r2 == 0.0) continue;
-                if (cell_coord(g, xj[0]) != cc[0] || cell_coord(g, xj[1]) != cc[1] ||
-                    cell_coord(g, xj[2]) != cc[2])
-                    continue;
                 int m = j;   // into the sorted list
 #pragma unroll
                 for (int k = 0; k < LUB_TAKE; ++k) {
@@ -151,29 +169,35 @@ k_lub_force(const double* __restrict__ x, const double* __restrict__ v,
                 if (j == 0x7fffffff) break;
                 double d[3] = { xi[0] - x[3 * (size_t)j], xi[1] - x[3 * (size_t)j + 1],
                                 xi[2] - x[3 * (size_t)j + 2] };
-                nearest_image_d(lc.pc, d[0], d[1], d[2]);
+                lub_image(lc, d);
                 const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
                 const double r = sqrt(r2);
                 double s = r / lc.a - 2.0;
                 if (s >= lc.s_cut) continue;
                 if (s < lc.s_min) s = lc.s_min;
                 const double ls = log(s);
-                const double cP = (1.0 / (4.0 * s) - 9.0 / 40.0 * ls) / lc.mu0;
-                const double cT = (-1.0 / 6.0 * ls) / lc.mu0;
+                const double cP = (0.25 / s - 9.0 / 40.0 * ls) * lc.imu0;
+                const double cT = (-1.0 / 6.0 * ls) * lc.imu0;
+                const double ri = 1.0 / r;
                 const double dv[3] = { v[3 * (size_t)i] - v[3 * (size_t)j],
                                        v[3 * (size_t)i + 1] - v[3 * (size_t)j + 1],
                                        v[3 * (size_t)i + 2] - v[3 * (size_t)j + 2] };
-                const double hd = (d[0] * dv[0] + d[1] * dv[1] + d[2] * dv[2]) / r;  // rhat . dv
+                const double hd = (d[0] * dv[0] + d[1] * dv[1] + d[2] * dv[2]) * ri;  // rhat . dv
                 for (int k3 = 0; k3 < 3; ++k3) {
-                    const double nrm = hd * d[k3] / r;                             // (rhat rhat dv)_k
+                    const double nrm = hd * d[k3] * ri;                             // (rhat rhat dv)_k
                     acc[k3] -= cP * nrm + cT * (dv[k3] - nrm);
                 }
             }
         }
     }
-    // over the 27 cells, fixed order
-    for (int w = 16; w > 0; w >>= 1)
-        for (int k = 0; k < 3; ++k) acc[k] += __shfl_xor(acc[k], w);
+    // over the 27 cells, fixed order: each row of 16 lanes by rotations, then the two
+    for (int k = 0; k < 3; ++k) {
+        acc[k] += row_rot<8>(acc[k]);
+        acc[k] += row_rot<4>(acc[k]);
+        acc[k] += row_rot<2>(acc[k]);
+        acc[k] += row_rot<1>(acc[k]);
+        acc[k] += __shfl_xor(acc[k], 16);
+    }
     if (q != 0) return;
     double fo[3];
     for (int k = 0; k < 3; ++k) fo[k] = (f_ext ? f_ext[3 * (size_t)i + k] : 0.0) + acc[k];
@@ -201,9 +225,9 @@ sd_status lub_forces_impl(const sd_params* p, const sd_lub* lub, int64_t n, cons
     sd_status st;
     void* buf = nullptr;
     const int buckets = lub_buckets(n);
-    if ((st = ws_get(WS_LUB, 4 * ((size_t)buckets + (size_t)n), &buf))) return st;
+    if ((st = ws_get(WS_LUB, 4 * (size_t)buckets + sizeof(int4) * (size_t)n, &buf))) return st;
     int* head = (int*)buf;
-    int* next = head + buckets;
+    int4* link = (int4*)(head + buckets);
     const int nn = (int)n;
     // a pair within the cutoff lies in neighbouring cells: the side exceeds the
     // cutoff by more than the rounding of x / h
@@ -222,17 +246,18 @@ sd_status lub_forces_impl(const sd_params* p, const sd_lub* lub, int64_t n, cons
     hipError_t e = launch_fill_i32(head, -1, buckets, hs);
     if (e != hipSuccess) return fail(SD_EDEVICE, "fill launch: %s", hipGetErrorString(e));
     hipLaunchKernelGGL(k_lub_insert, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, hs, x, nn, g,
-                       head, next);
+                       head, link);
     LubConst lc;
     lc.a = p->a;
-    lc.mu0 = 1.0 / (6.0 * M_PI * p->eta * p->a);
+    lc.imu0 = 6.0 * M_PI * p->eta * p->a;
     lc.s_cut = lub->s_cut;
     lc.s_min = lub->s_min;
     const double rc = (2.0 + lub->s_cut) * p->a;
     lc.rcut2 = rc * rc;
     lc.pc = pair_const(p);
+    lc.ibox = g.box > 2.001 * rc ? 1.0 / g.box : 0.0;
     hipLaunchKernelGGL(k_lub_force, dim3((unsigned)((n + 7) / 8)), dim3(256), 0, hs, x, v, f_ext, nn,
-                       g, head, next, lc, f_out, rec32, rec64);
+                       g, head, link, lc, f_out, rec32, rec64);
     if ((e = hipGetLastError()) != hipSuccess)
         return fail(SD_EDEVICE, "lubrication launch: %s", hipGetErrorString(e));
     return SD_OK;
