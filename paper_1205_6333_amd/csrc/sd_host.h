@@ -61,8 +61,8 @@ bool sym_fits(int64_t n, int block);
 // particles / wave-symmetric: N = 4500 19.9 / 22.2, 5324 25.3 / 26.9, 6007 30.5
 // / 29.6; FP64: N = 3500 18.8 / 22.5, 4000 23.8 / 23.6, 5000 34.3 / 30.4.
 // Microseconds per product, wave- / block-symmetric (compensated): N = 12000
-// 77.5 / -, 16384 126.8 / 124.2 (with one particle in ten overlapping 132.8 /
-// 162.5), 24576 301 / 243; plain sums (the block-symmetric loop is compiled
+// 77.5 / -, 16384 125.4 / 121.6 (with 0.4 near partners per particle 136.7 /
+// 154.1), 24576 301 / 243; plain sums (the block-symmetric loop is compiled
 // there) 16384 126 / 149, 20000 188 / 198, 24576 301 / 277.  FP64,
 // wave-symmetric / one-sided: N = 6000 39.7 / 72.6, 16384 199 / 301, 40000 1107
 // / 1730.
