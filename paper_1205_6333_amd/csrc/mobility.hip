@@ -70,7 +70,7 @@ PairLaunch shape_pair_launch(int n, int variant, int block, int splits, int ilp,
     if (splits > tiles) splits = tiles;
     const int tiles_per = (tiles + splits - 1) / splits;
     L.jchunk = tiles_per * block;
-    L.splits = (n + L.jchunk - 1) / L.jchunk;
+    L.splits = (n - 1) / L.jchunk + 1;   // (no overflow at n = 2^30)
     return L;
 }
 

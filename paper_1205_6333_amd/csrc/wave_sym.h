@@ -38,7 +38,8 @@ struct WaveShape {
     int nb, h, extra, lmax, chunks, splits;
 };
 
-// chunks per wave so that a launch has about `waves` waves
+// chunks per wave so that a launch has about `waves` waves (at most the whole
+// range; n up to 2^30, where the products exceed 32 bits)
 inline WaveShape wave_shape(int n, int B, int waves)
 {
     WaveShape s;
@@ -47,9 +48,11 @@ inline WaveShape wave_shape(int n, int B, int waves)
     s.extra = (s.nb >= 2 && (s.nb & 1) == 0) ? 1 : 0;
     s.lmax = (s.h + s.extra) * B;
     const int64_t total = (int64_t)s.nb * (s.lmax / 16);
-    const int64_t c = (total + waves - 1) / waves;
-    s.chunks = (int)(c < 1 ? 1 : c);
-    s.splits = (s.lmax + 64 * s.chunks - 1) / (64 * s.chunks);
+    int64_t c = (total + waves - 1) / waves;
+    if (c > s.lmax / 16) c = s.lmax / 16;
+    if (c < 1) c = 1;
+    s.chunks = (int)c;
+    s.splits = (int)((s.lmax + 64 * c - 1) / (64 * c));
     return s;
 }
 inline WaveShape wave_shape_of(const PairLaunch& L, int n)
