@@ -432,7 +432,10 @@ typedef struct sd_kernel_config {
                              20000) it runs kernels of its own instead, with
                              no shape to choose: small products as whole rows
                              in one launch, larger ones with each pair
-                             evaluated once */
+                             evaluated once in library workspace of about
+                             0.09 n^2 bytes (at most 1 GiB; the adjoint:
+                             0.4 n^2), or the kernel of this configuration
+                             where that cannot be allocated */
     int32_t block;        /* work-group size (64, 128 or 256; variant 2: 128,
                              256 or 512) */
     int32_t splits;       /* j-range splits (>= 1): extra work-groups per i-block */

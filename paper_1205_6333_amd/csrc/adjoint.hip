@@ -491,14 +491,16 @@ static sd_status adjoint_pass(const sd_params* p, int64_t n, const void* pos, co
 {
     sd_status st;
     void* partial = nullptr;
-    // each pair once wherever the j-side workspace fits (N = 50000 or so);
+    // each pair once wherever the j-side workspace fits (N = 50000 or so) and
+    // can be had;
     // microseconds per pass, one-sided / each pair once: FP64 N = 64 43 / 17,
     // 3001 134 / 29, 8192 352 / 125; FP32 N = 64 52 / 16, 3001 58 / 24, 8192
     // 131 / 86
     const PairLaunch W = plan_wave(n, 1);
     const size_t wb = wave_adjoint_bytes(W, n);
-    if (wb <= SYM_WORKSPACE_CAP) {
-        if ((st = ws_get(WS_ADJ_PARTIAL, wb, &partial))) return st;
+    st = wb <= SYM_WORKSPACE_CAP ? ws_get(WS_ADJ_PARTIAL, wb, &partial) : SD_ENOMEM;
+    if (st != SD_OK && st != SD_ENOMEM) return st;
+    if (st == SD_OK) {
         const hipError_t e = launch_wave_adjoint(W, p->tensor, prec == SD_FP64, pos, frc, lam4,
                                                  x64, (int)n, pair_const(p), partial, lam64, dt,
                                                  gpos, gforce, hs);
@@ -612,11 +614,11 @@ sd_status sd_run_adjoint(const sd_params* p, int64_t n, const double* x0, const 
         ck = xw;
     }
     void *traj = nullptr, *recs = nullptr, *lam4 = nullptr;
-    const PairLaunch L = plan_pair(precision, n);
+    PairLaunch L;
     StepBuffers sb;
     if ((st = ws_get(WS_ADJ_TRAJ, frame * (size_t)E, &traj)) ||
         (st = ws_get(WS_ADJ_REC, rec * (size_t)n * (size_t)E, &recs)) ||
-        (st = step_buffers(L, n, precision, &sb)) ||
+        (st = step_buffers(n, precision, &L, &sb)) ||
         (st = ws_get(WS_ADJ_PACK, rec * (size_t)n, &lam4)))
         return st;
     // lam lives in grad_x0 (initialised with grad_xN above)

@@ -309,10 +309,10 @@ sd_status sd_run_lub(const sd_params* p, const sd_lub* lub, int64_t n, double* x
     hipStream_t hs = (hipStream_t)stream;
     const bool f64 = precision == SD_FP64;
     const size_t rec = f64 ? 32 : 16;
-    const PairLaunch L = plan_pair(precision, n);
+    PairLaunch L;
     StepBuffers sb;
     void* F4 = nullptr;
-    if ((st = step_buffers(L, n, precision, &sb)) || (st = ws_get(WS_LUB_F, rec * (size_t)n, &F4)))
+    if ((st = step_buffers(n, precision, &L, &sb)) || (st = ws_get(WS_LUB_F, rec * (size_t)n, &F4)))
         return st;
     // per step: forces with the correction (written straight into the force
     // records of the pair kernel), then the step, which also stages the new

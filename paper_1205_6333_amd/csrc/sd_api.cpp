@@ -450,18 +450,17 @@ sd_status run_step(const sd_params* p, int64_t n, const double* x_in, double* x_
     return SD_OK;
 }
 
-sd_status step_buffers(const PairLaunch& L, int64_t n, int32_t prec, StepBuffers* sb)
+sd_status step_buffers(int64_t n, int32_t prec, PairLaunch* L, StepBuffers* sb)
 {
     sd_status st;
-    void *partial = nullptr, *stage = nullptr, *copy = nullptr;
+    void *stage = nullptr, *copy = nullptr;
     const size_t rec = ((size_t)n * (prec == SD_FP64 ? 32 : 16) + 255) & ~(size_t)255;
-    if ((st = ws_get(WS_PARTIAL, partial_bytes(L, n), &partial)) ||
+    if ((st = plan_product(prec, n, L, &sb->partial)) ||
         (st = ws_get(WS_STAGE, 2 * rec, &stage)))
         return st;
-    const bool apart = step_apart(L);
+    const bool apart = step_apart(*L);
     if (apart && (st = ws_get(WS_STEP_X, 3 * (size_t)n * sizeof(double), &copy)))
         return st;
-    sb->partial = (double*)partial;
     sb->pos[0] = (char*)stage;
     sb->pos[1] = apart ? (char*)stage + rec : (char*)stage;
     sb->copy = (double*)copy;
@@ -506,11 +505,11 @@ PairLaunch plan_wave(int64_t n, int ilp)
     return L;
 }
 
-PairLaunch plan_pair(int32_t prec, int64_t n)
+PairLaunch plan_pair(int32_t prec, int64_t n, bool general)
 {
     bool automatic = false;
     const sd_kernel_config c = choose_config(prec, n, &automatic);
-    if (automatic) {
+    if (automatic && !general) {
         const bool f64 = prec == SD_FP64;
         if (n < (f64 ? ROW_F64_END_N : ROW_F32_END_N)) {
             PairLaunch L{};
@@ -529,6 +528,19 @@ PairLaunch plan_pair(int32_t prec, int64_t n)
     L.acc = (prec == SD_FP64) ? 0 : c.kahan_block;
     if (prec == SD_FP32_PLAIN) L.acc = 0;
     return L;
+}
+
+sd_status plan_product(int32_t prec, int64_t n, PairLaunch* L, double** partial)
+{
+    void* ws = nullptr;
+    *L = plan_pair(prec, n);
+    sd_status st = ws_get(WS_PARTIAL, partial_bytes(*L, n), &ws);
+    if (st == SD_ENOMEM && L->variant == 3) {
+        *L = plan_pair(prec, n, true);
+        st = ws_get(WS_PARTIAL, partial_bytes(*L, n), &ws);
+    }
+    *partial = (double*)ws;
+    return st;
 }
 
 size_t partial_bytes(const PairLaunch& L, int64_t n)
@@ -631,9 +643,9 @@ sd_status mobility_apply(const sd_params* p, int64_t n, const void* pos, const v
         (st = check_ptr(vel, 8, "vel")))
         return st;
     hipStream_t hs = (hipStream_t)stream;
-    const PairLaunch L = plan_pair(precision, n);
-    void* partial = nullptr;
-    if ((st = ws_get(WS_PARTIAL, partial_bytes(L, n), &partial))) return st;
+    PairLaunch L;
+    double* partial = nullptr;
+    if ((st = plan_product(precision, n, &L, &partial))) return st;
     const void* pos_k = pos;
     if (box_side(p) > 0.0 && precision != SD_FP64) {  // fixed-point records for the box
         void* q = nullptr;
@@ -644,14 +656,13 @@ sd_status mobility_apply(const sd_params* p, int64_t n, const void* pos, const v
         pos_k = q;
     }
     bool merged = false;
-    if ((st = run_pair(p, n, pos_k, force, nullptr, precision, (double*)partial, L, hs, vel,
-                       &merged)))
+    if ((st = run_pair(p, n, pos_k, force, nullptr, precision, partial, L, hs, vel, &merged)))
         return st;
     if (merged) return SD_OK;   // the pair-symmetric kernel's fold wrote vel
     hipError_t e = (precision == SD_FP64)
-                       ? launch_merge_f64((double*)partial, L.splits, (int)n, (const double4*)force,
+                       ? launch_merge_f64(partial, L.splits, (int)n, (const double4*)force,
                                           1.0 / (6.0 * M_PI * p->eta * p->a), vel, hs)
-                       : launch_merge_f32((double*)partial, L.splits, (int)n, (const float4*)force,
+                       : launch_merge_f32(partial, L.splits, (int)n, (const float4*)force,
                                           1.0 / (6.0 * M_PI * p->eta * p->a), vel, hs);
     if (e != hipSuccess) return fail(SD_EDEVICE, "merge kernel launch: %s", hipGetErrorString(e));
     return SD_OK;
@@ -687,9 +698,9 @@ sd_status sd_step(const sd_params* p, int64_t n, double* x, const void* force, d
     if (step_index < 0) return fail(SD_EINVAL, "step_index must be >= 0");
     if (v_out && (uintptr_t)v_out % 8) return fail(SD_EALIGN, "v_out is not 8-byte aligned");
     hipStream_t hs = (hipStream_t)stream;
-    const PairLaunch L = plan_pair(precision, n);
+    PairLaunch L;
     StepBuffers sb;
-    if ((st = step_buffers(L, n, precision, &sb)) ||
+    if ((st = step_buffers(n, precision, &L, &sb)) ||
         (st = steps_begin(p, n, x, 1, precision, L, &sb, hs)))
         return st;
     return steps_next(p, n, force, integrator == SD_AB2 ? v_prev : nullptr, v_out, dt,
@@ -713,9 +724,10 @@ sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, do
                              hipSuccess)
         return fail(SD_EDEVICE, "checkpoint copy failed");
     if (steps == 0) return SD_OK;
-    const PairLaunch L = plan_pair(precision, n);
+    PairLaunch L;
     StepBuffers sb;
-    if ((st = step_buffers(L, n, precision, &sb))) return st;
+    if ((st = step_buffers(n, precision, &L, &sb))) return st;
+    const StepBuffers first = sb;
     double* vp = integrator == SD_AB2 ? v_prev : nullptr;
     int64_t done = 0;
     const int32_t gmode = g_graph_mode.load();
@@ -744,7 +756,7 @@ sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, do
         key.prec = precision;
         key.L = L;
         // (the capture starts from the first record array whatever ran before)
-        if ((st = step_buffers(L, n, precision, &sb))) return st;
+        sb = first;
         key.partial = sb.partial;
         key.stage = sb.pos[0];
         key.copy = sb.copy;

@@ -78,7 +78,12 @@ void set_tuned_config(int32_t prec, int64_t n, const sd_kernel_config* c);
 sd_status check_config(int32_t prec, const sd_kernel_config& c);
 
 PairConst pair_const(const sd_params* p);
-PairLaunch plan_pair(int32_t prec, int64_t n);
+// general: none of the automatic choice's own kernels
+PairLaunch plan_pair(int32_t prec, int64_t n, bool general = false);
+// The plan together with its workspace.  Where the wave-symmetric kernels'
+// (up to 1 GiB, against some tens of MiB) cannot be had, the general kernel is
+// planned.
+sd_status plan_product(int32_t prec, int64_t n, PairLaunch* L, double** partial);
 // a wave-symmetric launch (variant 3) with ilp particles per lane
 PairLaunch plan_wave(int64_t n, int ilp);
 size_t partial_bytes(const PairLaunch& L, int64_t n);
@@ -108,7 +113,7 @@ struct StepBuffers {
     double* cur = nullptr;                 // the current positions
     double* other = nullptr;               // where the next step puts them
 };
-sd_status step_buffers(const PairLaunch& L, int64_t n, int32_t prec, StepBuffers* sb);
+sd_status step_buffers(int64_t n, int32_t prec, PairLaunch* L, StepBuffers* sb);
 sd_status steps_begin(const sd_params* p, int64_t n, double* x, int64_t steps, int32_t prec,
                       const PairLaunch& L, StepBuffers* sb, hipStream_t st);
 // more: another step follows (its records are staged)
