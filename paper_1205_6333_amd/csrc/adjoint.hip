@@ -471,6 +471,12 @@ hipError_t launch_adjoint_f64(const PairLaunch& L, int tensor, const double4* po
     return hipGetLastError();
 }
 
+// Records of a checkpoint segment that sd_run_adjoint keeps besides the segment's
+// frames (two thirds of their size in FP32, four thirds in FP64): all that the
+// usual tens of steps of some thousand particles need.  Longer segments stage each
+// state again, one more launch per step.
+constexpr size_t ADJ_REC_CAP = (size_t)64 << 20;
+
 // launch shape of the adjoint pair kernel: 256-thread groups, splits as the
 // forward product's automatic choice
 static PairLaunch plan_adjoint(int32_t prec, int64_t n)
@@ -617,10 +623,13 @@ sd_status sd_run_adjoint(const sd_params* p, int64_t n, const double* x0, const 
     PairLaunch L;
     StepBuffers sb;
     if ((st = ws_get(WS_ADJ_TRAJ, frame * (size_t)E, &traj)) ||
-        (st = ws_get(WS_ADJ_REC, rec * (size_t)n * (size_t)E, &recs)) ||
         (st = step_buffers(n, precision, &L, &sb)) ||
         (st = ws_get(WS_ADJ_PACK, rec * (size_t)n, &lam4)))
         return st;
+    // a segment's records are kept while they are small (ADJ_REC_CAP); else the
+    // time loop's two arrays serve
+    const size_t seg_recs = rec * (size_t)n * (size_t)std::min(E, steps);
+    if (seg_recs > ADJ_REC_CAP || ws_get(WS_ADJ_REC, seg_recs, &recs) != SD_OK) recs = nullptr;
     // lam lives in grad_x0 (initialised with grad_xN above)
     double* lam = grad_x0;
     double* T = (double*)traj;
@@ -635,7 +644,9 @@ sd_status sd_run_adjoint(const sd_params* p, int64_t n, const double* x0, const 
         // states), each step into the next frame
         const double* x0k = ck + m * (size_t)seg;
         auto state = [&](int64_t k) { return k == k0 ? x0k : T + m * (size_t)(k - k0); };
-        auto record = [&](int64_t k) { return R + rec * (size_t)n * (size_t)(k - k0); };
+        auto record = [&](int64_t k) {
+            return R ? R + rec * (size_t)n * (size_t)(k - k0) : sb.pos[(k - k0) & 1];
+        };
         hipError_t e = launch_stage(f64, x0k, record(k0), (int)n, 0.0, nullptr, hs);
         if (e != hipSuccess) return fail(SD_EDEVICE, "stage launch: %s", hipGetErrorString(e));
         for (int64_t k = k0; k + 1 < k1; ++k)
@@ -644,6 +655,9 @@ sd_status sd_run_adjoint(const sd_params* p, int64_t n, const double* x0, const 
                                hs)))
                 return st;
         for (int64_t k = k1 - 1; k >= k0; --k) {
+            if (!R && (e = launch_stage(f64, state(k), record(k), (int)n, 0.0, nullptr, hs)) !=
+                          hipSuccess)
+                return fail(SD_EDEVICE, "stage launch: %s", hipGetErrorString(e));
             if (!have_lam4) {
                 e = f64 ? launch_pack_f64(lam, (double4*)lam4, (int)n, hs)
                         : launch_pack_f32(lam, (float4*)lam4, (int)n, hs);

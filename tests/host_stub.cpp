@@ -58,6 +58,13 @@ size_t stub_largest()
     g_largest = 0;
     return b;
 }
+// bytes allocated now
+size_t stub_total()
+{
+    size_t b = 0;
+    for (const auto& kv : g_blocks) b += kv.second;
+    return b;
+}
 
 // ---- runtime
 void** __hipRegisterFatBinary(const void*)

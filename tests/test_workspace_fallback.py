@@ -41,3 +41,18 @@ for st in (apply(60000, F64), apply(6007, KAHAN), adjoint(3001, F64), step(300, 
     assert len(out) == 4
     for line in out:
         assert line.startswith("True [] workspace allocation"), line
+
+
+@pytest.mark.parametrize("prec", ["KAHAN", "F64"])
+def test_long_segments_hold_frames_only(stub, prec):
+    """A trajectory gradient with one long checkpoint segment allocates its frames
+    and, beside them, less than another half: 2000 steps of 8192 particles."""
+    out = stub_util.child(stub, """
+n, steps = 8192, 2000
+alloc_limit(1 << 40)
+st = run_adjoint(n, %s, steps, steps)
+L.stub_total.restype = C.c_size_t
+print(st, L.stub_total() / (24.0 * n * steps))
+""" % prec).split("\n")
+    st, ratio = out[0].split(" ")
+    assert st == "0" and float(ratio) < 1.5, out[0]
