@@ -82,8 +82,7 @@ typedef enum sd_precision {
                              over the i-block, rounded to FP32 once per i-block
                              and j and added in FP64 */
     SD_FP64 = 1,          /* FP64 throughout */
-    SD_FP32_PLAIN = 2     /* FP32 evaluation and plain FP32 accumulation (the
-                             automatic choice may sum more accurately) */
+    SD_FP32_PLAIN = 2     /* FP32 evaluation and plain FP32 accumulation */
 } sd_precision;
 
 typedef enum sd_integrator {
@@ -428,9 +427,9 @@ typedef struct sd_kernel_config {
                              n = 16384 on (block 256, ilp 2, kahan_block
                              32 for SD_FP32_KAHAN) while that workspace
                              stays within 1 GiB.  Where the automatic choice
-                             names variant 0 (and for SD_FP32_PLAIN below n =
-                             20000) it runs kernels of its own instead, with
-                             no shape to choose: small products as whole rows
+                             names variant 0 in FP64 or for SD_FP32_KAHAN it
+                             runs kernels of its own instead, with no shape
+                             to choose: small products as whole rows
                              in one launch, larger ones with each pair
                              evaluated once in library workspace of about
                              0.09 n^2 bytes (at most 1 GiB; the adjoint:

@@ -509,7 +509,9 @@ PairLaunch plan_pair(int32_t prec, int64_t n, bool general)
 {
     bool automatic = false;
     const sd_kernel_config c = choose_config(prec, n, &automatic);
-    if (automatic && !general) {
+    // (plain FP32 sums are the general kernels': what a caller compares with the
+    // compensated ones)
+    if (automatic && !general && prec != SD_FP32_PLAIN) {
         const bool f64 = prec == SD_FP64;
         if (n < (f64 ? ROW_F64_END_N : ROW_F32_END_N)) {
             PairLaunch L{};
@@ -519,7 +521,7 @@ PairLaunch plan_pair(int32_t prec, int64_t n, bool general)
             L.splits = 1;
             return L;
         }
-        if (f64 || n < (prec == SD_FP32_KAHAN ? SYM_MIN_N : WAVE_PLAIN_END_N)) {
+        if (f64 || n < SYM_MIN_N) {
             const PairLaunch W = plan_wave(n, 2);
             if (partial_bytes(W, n) <= SYM_WORKSPACE_CAP) return W;
         }

@@ -51,7 +51,8 @@ constexpr size_t SYM_WORKSPACE_CAP = (size_t)1 << 30;
 // Smallest n for which the automatic configuration takes variant 2.
 constexpr int64_t SYM_MIN_N = 16384;
 bool sym_fits(int64_t n, int block);
-// What the automatic choice runs beyond the configurations of sd.h.
+// What the automatic choice runs beyond the configurations of sd.h, in FP64 and
+// with compensated FP32 sums.
 //
 // Rows in one launch (variant 4) below ROW_*_END_N, two particles per
 // work-group from ROW_ILP2_MIN_N on.  Above, each pair once: the wave-symmetric
@@ -62,14 +63,12 @@ bool sym_fits(int64_t n, int block);
 // / 29.6; FP64: N = 3500 18.8 / 22.5, 4000 23.8 / 23.6, 5000 34.3 / 30.4.
 // Microseconds per product, wave- / block-symmetric (compensated): N = 12000
 // 77.5 / -, 16384 125.4 / 121.6 (with 0.4 near partners per particle 136.7 /
-// 154.1), 24576 301 / 243; plain sums (the block-symmetric loop is compiled
-// there) 16384 126 / 149, 20000 188 / 198, 24576 301 / 277.  FP64,
+// 154.1), 24576 301 / 243.  FP64,
 // wave-symmetric / one-sided: N = 6000 39.7 / 72.6, 16384 199 / 301, 40000 1107
 // / 1730.
 constexpr int64_t ROW_F32_END_N = 5900;
 constexpr int64_t ROW_F64_END_N = 4000;
 constexpr int64_t ROW_ILP2_MIN_N = 1300;
-constexpr int64_t WAVE_PLAIN_END_N = 20000;
 // The configuration for n particles; *automatic (may be null) receives whether
 // it is the automatic choice (nothing forced, no tuned shape for the size).
 sd_kernel_config choose_config(int32_t prec, int64_t n, bool* automatic = nullptr);
