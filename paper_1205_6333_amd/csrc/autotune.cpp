@@ -153,14 +153,15 @@ extern "C" sd_status sd_autotune(const sd_params* p, int64_t n, int32_t precisio
     std::vector<Cand> res;
     for (const sd_kernel_config& c : candidates(precision, n)) {
         if (check_config(precision, c) != SD_OK) continue;
-        // (the automatic choice is timed as the library runs it, not forced)
-        const bool automatic = same_config(c, default_config(precision, n));
-        if (automatic) set_tuned_config(precision, n, nullptr);
-        if ((st = sd_set_kernel_config(precision, automatic ? nullptr : &c))) break;
-        if ((st = mobility_apply(p, n, pos, frc, vel, precision, stream))) break;
+        // (the automatic choice is timed as the library runs it, not forced, and the
+        // tuned shape of the size class stays until a faster one is known)
+        const PlanMode mode =
+            same_config(c, default_config(precision, n)) ? PLAN_AUTOMATIC : PLAN_CHOSEN;
+        if ((st = sd_set_kernel_config(precision, &c))) break;
+        if ((st = run_product(p, n, pos, frc, vel, precision, mode, hs))) break;
         (void)hipEventRecord(e0, hs);
         for (int r = 0; r < 3; ++r)
-            if ((st = mobility_apply(p, n, pos, frc, vel, precision, stream))) break;
+            if ((st = run_product(p, n, pos, frc, vel, precision, mode, hs))) break;
         (void)hipEventRecord(e1, hs);
         if (st) break;
         if (hipEventSynchronize(e1) != hipSuccess) {

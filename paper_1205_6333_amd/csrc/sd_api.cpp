@@ -490,6 +490,33 @@ sd_status steps_next(const sd_params* p, int64_t n, const void* frc, double* v_p
     return r;
 }
 
+sd_status run_product(const sd_params* p, int64_t n, const void* pos, const void* frc, double* vel,
+                      int32_t prec, PlanMode mode, hipStream_t st)
+{
+    sd_status r;
+    PairLaunch L;
+    double* partial = nullptr;
+    if ((r = plan_product(prec, n, &L, &partial, mode))) return r;
+    const void* pos_k = pos;
+    if (box_side(p) > 0.0 && prec != SD_FP64) {  // fixed-point records for the box
+        void* q = nullptr;
+        if ((r = ws_get(WS_QPOS, (size_t)n * 16, &q))) return r;
+        hipError_t e = launch_stage_q_from_f32((const float4*)pos, (float4*)q, (int)n,
+                                               box_side(p), st);
+        if (e != hipSuccess) return fail(SD_EDEVICE, "stage launch: %s", hipGetErrorString(e));
+        pos_k = q;
+    }
+    bool merged = false;
+    if ((r = run_pair(p, n, pos_k, frc, nullptr, prec, partial, L, st, vel, &merged))) return r;
+    if (merged) return SD_OK;   // the pair-symmetric kernel's fold wrote vel
+    const double mu0 = 1.0 / (6.0 * M_PI * p->eta * p->a);
+    hipError_t e = prec == SD_FP64
+                       ? launch_merge_f64(partial, L.splits, (int)n, (const double4*)frc, mu0, vel, st)
+                       : launch_merge_f32(partial, L.splits, (int)n, (const float4*)frc, mu0, vel, st);
+    if (e != hipSuccess) return fail(SD_EDEVICE, "merge kernel launch: %s", hipGetErrorString(e));
+    return SD_OK;
+}
+
 PairLaunch plan_wave(int64_t n, int ilp)
 {
     PairLaunch L{};
@@ -505,13 +532,14 @@ PairLaunch plan_wave(int64_t n, int ilp)
     return L;
 }
 
-PairLaunch plan_pair(int32_t prec, int64_t n, bool general)
+PairLaunch plan_pair(int32_t prec, int64_t n, PlanMode mode)
 {
-    bool automatic = false;
-    const sd_kernel_config c = choose_config(prec, n, &automatic);
+    bool automatic = true;
+    const sd_kernel_config c = mode == PLAN_AUTOMATIC ? default_config(prec, n)
+                                                      : choose_config(prec, n, &automatic);
     // (plain FP32 sums are the general kernels': what a caller compares with the
     // compensated ones)
-    if (automatic && !general && prec != SD_FP32_PLAIN) {
+    if (automatic && mode != PLAN_GENERAL && prec != SD_FP32_PLAIN) {
         const bool f64 = prec == SD_FP64;
         if (n < (f64 ? ROW_F64_END_N : ROW_F32_END_N)) {
             PairLaunch L{};
@@ -532,13 +560,13 @@ PairLaunch plan_pair(int32_t prec, int64_t n, bool general)
     return L;
 }
 
-sd_status plan_product(int32_t prec, int64_t n, PairLaunch* L, double** partial)
+sd_status plan_product(int32_t prec, int64_t n, PairLaunch* L, double** partial, PlanMode mode)
 {
     void* ws = nullptr;
-    *L = plan_pair(prec, n);
+    *L = plan_pair(prec, n, mode);
     sd_status st = ws_get(WS_PARTIAL, partial_bytes(*L, n), &ws);
     if (st == SD_ENOMEM && L->variant == 3) {
-        *L = plan_pair(prec, n, true);
+        *L = plan_pair(prec, n, PLAN_GENERAL);
         st = ws_get(WS_PARTIAL, partial_bytes(*L, n), &ws);
     }
     *partial = (double*)ws;
@@ -644,30 +672,7 @@ sd_status mobility_apply(const sd_params* p, int64_t n, const void* pos, const v
     if ((st = check_ptr(pos, al, "pos")) || (st = check_ptr(force, al, "force")) ||
         (st = check_ptr(vel, 8, "vel")))
         return st;
-    hipStream_t hs = (hipStream_t)stream;
-    PairLaunch L;
-    double* partial = nullptr;
-    if ((st = plan_product(precision, n, &L, &partial))) return st;
-    const void* pos_k = pos;
-    if (box_side(p) > 0.0 && precision != SD_FP64) {  // fixed-point records for the box
-        void* q = nullptr;
-        if ((st = ws_get(WS_QPOS, (size_t)n * 16, &q))) return st;
-        hipError_t e = launch_stage_q_from_f32((const float4*)pos, (float4*)q, (int)n,
-                                               box_side(p), hs);
-        if (e != hipSuccess) return fail(SD_EDEVICE, "stage launch: %s", hipGetErrorString(e));
-        pos_k = q;
-    }
-    bool merged = false;
-    if ((st = run_pair(p, n, pos_k, force, nullptr, precision, partial, L, hs, vel, &merged)))
-        return st;
-    if (merged) return SD_OK;   // the pair-symmetric kernel's fold wrote vel
-    hipError_t e = (precision == SD_FP64)
-                       ? launch_merge_f64(partial, L.splits, (int)n, (const double4*)force,
-                                          1.0 / (6.0 * M_PI * p->eta * p->a), vel, hs)
-                       : launch_merge_f32(partial, L.splits, (int)n, (const float4*)force,
-                                          1.0 / (6.0 * M_PI * p->eta * p->a), vel, hs);
-    if (e != hipSuccess) return fail(SD_EDEVICE, "merge kernel launch: %s", hipGetErrorString(e));
-    return SD_OK;
+    return run_product(p, n, pos, force, vel, precision, PLAN_CHOSEN, (hipStream_t)stream);
 }
 
 // mode of launch_merge_integrate for the step with a global index

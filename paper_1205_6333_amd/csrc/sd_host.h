@@ -77,12 +77,19 @@ void set_tuned_config(int32_t prec, int64_t n, const sd_kernel_config* c);
 sd_status check_config(int32_t prec, const sd_kernel_config& c);
 
 PairConst pair_const(const sd_params* p);
-// general: none of the automatic choice's own kernels
-PairLaunch plan_pair(int32_t prec, int64_t n, bool general = false);
+// PLAN_CHOSEN: the forced, tuned or automatic choice; PLAN_GENERAL: the same
+// without the automatic choice's own kernels; PLAN_AUTOMATIC: the automatic choice
+// whatever is forced or tuned.
+enum PlanMode { PLAN_CHOSEN, PLAN_GENERAL, PLAN_AUTOMATIC };
+PairLaunch plan_pair(int32_t prec, int64_t n, PlanMode mode = PLAN_CHOSEN);
 // The plan together with its workspace.  Where the wave-symmetric kernels'
 // (up to 1 GiB, against some tens of MiB) cannot be had, the general kernel is
 // planned.
-sd_status plan_product(int32_t prec, int64_t n, PairLaunch* L, double** partial);
+sd_status plan_product(int32_t prec, int64_t n, PairLaunch* L, double** partial,
+                       PlanMode mode = PLAN_CHOSEN);
+// mobility_apply with checked arguments
+sd_status run_product(const sd_params* p, int64_t n, const void* pos, const void* frc, double* vel,
+                      int32_t prec, PlanMode mode, hipStream_t st);
 // a wave-symmetric launch (variant 3) with ilp particles per lane
 PairLaunch plan_wave(int64_t n, int ilp);
 size_t partial_bytes(const PairLaunch& L, int64_t n);
