@@ -24,9 +24,12 @@
 
 namespace sd {
 
-// Cells and buckets.  Free space: cell floor(x / h) per axis (clamped to 2^30:
-// particles further out share the outermost cells, which costs time only);
-// periodic: dims cells per axis tile the cube.
+// Cells and buckets.  Free space: cell floor(x / h) per axis modulo 2^32, up to
+// LUB_CELL_END cells (about 2^40) from the origin, where FP64 positions resolve
+// 1e-3 a: particles further out share the outermost cells, which costs time only
+// (with an end of 2^30, 20000 particles at 1e10 a took 51 ms per call, at the origin
+// 0.05).  Periodic: dims cells per axis tile the cube.
+constexpr double LUB_CELL_END = 1097364144128.0;   // 2^40 - 2^31: not near cell 0 mod 2^32
 struct CellHash {
     double ih;       // 1 / cell side
     double box;      // periodic cubic box side, 0 = free space
@@ -58,7 +61,7 @@ __device__ __forceinline__ int cell_coord(const CellHash& g, double v)
         const int c = (int)fmin(fmax(floor(v * g.ih), 0.0), 1073741824.0);
         return c >= g.dims ? g.dims - 1 : c;
     }
-    return (int)fmin(fmax(floor(v * g.ih), -1073741824.0), 1073741824.0);
+    return (int)(unsigned)(long long)fmin(fmax(floor(v * g.ih), -LUB_CELL_END), LUB_CELL_END);
 }
 
 // (neighbouring cells of a row along x are neighbouring buckets: nine cache
@@ -88,7 +91,7 @@ __global__ void __launch_bounds__(256) k_lub_insert(const double* __restrict__ x
 __device__ __forceinline__ bool axis_neighbour(const CellHash& g, int c, int m, int& out)
 {
     if (!(g.box > 0.0)) {
-        out = c - 1 + m;
+        out = (int)((unsigned)c - 1u + (unsigned)m);
         return true;
     }
     if (g.dims < 3) {
@@ -230,10 +233,11 @@ sd_status lub_forces_impl(const sd_params* p, const sd_lub* lub, int64_t n, cons
     int4* link = (int4*)(head + buckets);
     const int nn = (int)n;
     // a pair within the cutoff lies in neighbouring cells: the side exceeds the
-    // cutoff by more than the rounding of x / h
-    const double hmin = (2.0 + lub->s_cut) * p->a * (1.0 + 1e-6);
+    // cutoff by more than the rounding of x / h (2^-12 cells at LUB_CELL_END in
+    // free space)
     CellHash g;
     g.box = box_side(p);
+    const double hmin = (2.0 + lub->s_cut) * p->a * (1.0 + (g.box > 0.0 ? 1e-6 : 5e-4));
     g.mask = (unsigned)buckets - 1u;
     g.dims = 0;
     double h = hmin;
