@@ -116,7 +116,12 @@ __device__ __forceinline__ bool axis_neighbour(const CellHash& g, int c, int m, 
 // scatter, sort, forces with one lane per particle) were used before: N = 100 60 ->
 // 12, 5000 83 -> 13, 20000 82 -> 18, 65536 98 -> 45, 200000 156 -> 139; the lattice 253
 // -> 233.
-constexpr int LUB_TAKE = 4;
+// Crowded cells (spheres that overlap: without overlap a cell holds five) are what
+// sets LUB_TAKE, each further walk being a chain from its start.  Microseconds, ten
+// launches / LUB_TAKE 4 / 8, random positions: 20000 with 8 per cell 401 / 133 / 116,
+// with 100 3854 / 3399 / 1967; one cell of 64 185 / 348 / 237, of 2000 127e3 / 249e3 /
+// 142e3; the lattice 253 / 232 / 234, 20000 at a volume fraction of 0.3 - / 31 / 31.
+constexpr int LUB_TAKE = 8;
 
 __global__ void __launch_bounds__(256)
 k_lub_force(const double* __restrict__ x, const double* __restrict__ v,
