@@ -156,10 +156,9 @@ def _time_path(sd, pos, frc, vel, prec, steps, warmup, prewarm_s=0.0):
     return t1 - t0, kern_ms / max(1, launches), ev0.elapsed_time(ev1), per, untimed
 
 
-def _kernel_name(cfg):
-    if cfg.get("variant") == 2:
-        return "k_pair_f32_sym_asm" if cfg.get("kahan_block") in (16, 32) else "k_pair_f32_sym"
-    return "k_pair_f32_lds" if cfg.get("variant") == 0 else "k_pair_f32_smem"
+def _kernel_shape(name, cfg):
+    """What runs: the configuration, or only the name of a kernel that has none."""
+    return cfg if name.startswith("k_pair_") else {"name": name}
 
 
 def _small_product(sd, W, dev, args):
@@ -171,7 +170,8 @@ def _small_product(sd, W, dev, args):
     f = W.gaussian_forces(n, seed=2)
     pos, frc = _to4(x, torch.float32, dev), _to4(f, torch.float32, dev)
     vel = torch.empty((n, 3), dtype=torch.float64, device=dev)
-    cfg = sd.sd_get_kernel_config(sd.SD_FP32_KAHAN, n)
+    name = sd.sd_kernel_name(sd.SD_FP32_KAHAN, n)
+    cfg = _kernel_shape(name, sd.sd_get_kernel_config(sd.SD_FP32_KAHAN, n))
     steps = max(20, args.steps)
     print("bench: timing fp32-kahan n=%d %s" % (n, cfg), file=sys.stderr, flush=True)
     wall, kern_ms, _, per, _ = _time_path(sd, pos, frc, vel, sd.SD_FP32_KAHAN, steps, 20,
@@ -180,7 +180,7 @@ def _small_product(sd, W, dev, args):
     med = float(np.median(per)) if per else kern_ms
     return {"value": pairs * steps / wall / 1e9, "unit": "G pair-interactions/s",
             "steps": steps, "ms_per_step": wall * 1e3 / steps, "pair_kernel_ms": kern_ms,
-            "pair_kernel_ms_median": med, "kernel": cfg, "kernel_name": _kernel_name(cfg),
+            "pair_kernel_ms_median": med, "kernel": cfg, "kernel_name": name,
             "frac_median": FLOP_PER_PAIR * pairs / (med * 1e-3) / 1e12 / PEAK_FP32_TFLOPS}
 
 
@@ -655,7 +655,8 @@ def main():
     tune_report = None
     if args.tune:
         tune_report = sd.sd_autotune(n, precision=sd.SD_FP32_KAHAN)
-    cfg = sd.sd_get_kernel_config(sd.SD_FP32_KAHAN, n)
+    name = sd.sd_kernel_name(sd.SD_FP32_KAHAN, n)
+    cfg = _kernel_shape(name, sd.sd_get_kernel_config(sd.SD_FP32_KAHAN, n))
     print("bench: timing fp32-kahan %s" % cfg, file=sys.stderr, flush=True)
     wall, kern_ms, ev_ms, per, untimed = _time_path(sd, pos32, frc32, vel, sd.SD_FP32_KAHAN,
                                                     args.steps, args.warmup, args.prewarm_s)
@@ -683,7 +684,7 @@ def main():
                        "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS,
                        "traffic": _measured_traffic(n, cfg),
                        "flop_per_pair": FLOP_PER_PAIR,
-                       "kernel": "pair kernel (%s)" % _kernel_name(cfg)}
+                       "kernel": "pair kernel (%s)" % name}
     valu = _measured_valu(n, cfg)
     if valu is not None:
         instr, flops = valu

@@ -453,6 +453,10 @@ sd_status sd_set_kernel_config(int32_t precision, const sd_kernel_config* cfg);
  * choice's own kernels are not configurations, see variant; forcing what is
  * returned here runs the general kernel of that shape). */
 sd_status sd_get_kernel_config(int32_t precision, int64_t n, sd_kernel_config* out);
+/* Name of the pair kernel that mobility_apply would launch for n particles (with
+ * its workspace available), the automatic choice's own kernels included; NULL
+ * for an unknown precision or n out of range. */
+const char* sd_kernel_name(int32_t precision, int64_t n);
 
 /*
  * sd_autotune -- time candidate configurations on n synthetic particles and

@@ -128,6 +128,8 @@ def lib() -> ctypes.CDLL:
             fn.restype = ctypes.c_int32
         L.sd_status_string.restype = ctypes.c_char_p
         L.sd_last_error.restype = ctypes.c_char_p
+        L.sd_kernel_name.argtypes = [i32, i64]
+        L.sd_kernel_name.restype = ctypes.c_char_p
         L.sd_batch_particles.argtypes = [vp]
         L.sd_batch_particles.restype = ctypes.c_int64
         _lib = L
@@ -521,6 +523,14 @@ def sd_get_kernel_config(precision: int, n: int) -> dict:
     c = SdKernelConfig()
     check(lib().sd_get_kernel_config(int(precision), int(n), ctypes.byref(c)))
     return c.as_dict()
+
+
+def sd_kernel_name(precision: int, n: int) -> str:
+    """Name of the pair kernel that mobility_apply would launch."""
+    name = lib().sd_kernel_name(int(precision), int(n))
+    if name is None:
+        check(SD_EINVAL)
+    return name.decode()
 
 
 def sd_autotune(n: int, *, params: SdParams = None, precision: int = SD_FP32_KAHAN,

@@ -876,6 +876,20 @@ sd_status sd_get_kernel_config(int32_t precision, int64_t n, sd_kernel_config* o
     return SD_OK;
 }
 
+const char* sd_kernel_name(int32_t precision, int64_t n)
+{
+    if (check_precision(precision) || check_n(n)) return nullptr;
+    const PairLaunch L = plan_pair(precision, n);
+    const bool f64 = precision == SD_FP64;
+    switch (L.variant) {
+    case 4: return f64 ? "k_row_f64" : "k_row_f32";
+    case 3: return f64 ? "k_wave_f64" : "k_wave_f32";
+    case 2: return L.acc == 16 || L.acc == 32 ? "k_pair_f32_sym_asm" : "k_pair_f32_sym";
+    case 1: return "k_pair_f32_smem";
+    default: return f64 ? "k_pair_f64_lds" : "k_pair_f32_lds";
+    }
+}
+
 sd_status sd_profile_enable(int32_t on)
 {
     std::lock_guard<std::mutex> lk(g_mu);
