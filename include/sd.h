@@ -198,10 +198,10 @@ sd_status sd_run(const sd_params* p, int64_t n, double* x, const void* force, do
  * requested and profiling is off: 0 = every kernel launched on the stream;
  * 1 (default) = whichever is faster for n (launching, at every n); 2 = chunks
  * of 16 steps are captured once into a HIP graph (on a private capture stream,
- * kernel nodes only) and replayed on the caller's stream, at every n.  The results are identical in every mode (the same kernels in the same
- * order).  The captured graph is cached per device and rebuilt when any
- * argument, size, parameter, kernel shape or workspace it captured changes;
- * sd_release frees it.
+ * kernel nodes only) and replayed on the caller's stream, at every n.  The
+ * results are identical in every mode (the same kernels in the same order).
+ * The captured graph is cached per device and rebuilt when any argument, size,
+ * parameter, kernel shape or workspace it captured changes; sd_release frees it.
  */
 sd_status sd_set_graph_mode(int32_t mode);
 

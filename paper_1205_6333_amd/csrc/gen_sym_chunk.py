@@ -41,7 +41,7 @@ records (PER):
   from the negated compensation NC of the previous block):
     t = S + Y; NC = Y - (t - S); S = t.
 
-The wave-symmetric form (wave_chunk_asm.h, k_wave_f32_asm in wave_f32.hip) is
+The wave-symmetric form (wave_chunk_asm.h, k_wave_f32 in wave_f32.hip) is
 one chunk per statement with shorter FP32 sums:
   i side: Y_l is a block of four terms (started by a multiply), added to Y2_l,
   which started from NC; after the 16 steps t = S + Y2; NC = Y2 - (t - S); S = t

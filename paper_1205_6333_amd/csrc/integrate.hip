@@ -1,6 +1,6 @@
 // integrate.hip -- O(N) kernels of the time loop (Sec. 3.1, step 1) and small
 // helpers: FP64 -> FP32 staging of positions, split merge fused with the
-// Euler / AB2 position update, packing and axpy for the adjoint loop.
+// Euler / AB2 position update, packing for the adjoint loop.
 #include "pair_terms.h"
 #include "sd_internal.h"
 
@@ -52,21 +52,6 @@ k_merge_integrate(const double* __restrict__ partial, int S, int n, const F4* __
     if (pos_next) put_pos(pos_next, i, xn[0], xn[1], xn[2], qs);
 }
 
-__global__ void __launch_bounds__(256) k_sum_partials(const double* __restrict__ partial, int S,
-                                                      int n, double* __restrict__ out,
-                                                      double scale, int accumulate)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    double g[3] = { 0.0, 0.0, 0.0 };
-    add_split_rows(partial, S, n, i, g[0], g[1], g[2]);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const size_t e = 3 * (size_t)i + k;
-        out[e] = accumulate ? out[e] + scale * g[k] : scale * g[k];
-    }
-}
-
 template <typename P4>
 __global__ void __launch_bounds__(256) k_pack(const double* __restrict__ v, P4* __restrict__ out,
                                               int n)
@@ -74,13 +59,6 @@ __global__ void __launch_bounds__(256) k_pack(const double* __restrict__ v, P4* 
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     put_pos(out, i, v[3 * (size_t)i], v[3 * (size_t)i + 1], v[3 * (size_t)i + 2], 0.0);
-}
-
-__global__ void __launch_bounds__(256) k_axpy(double s, const double* __restrict__ x,
-                                              double* __restrict__ y, int64_t m)
-{
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k < m) y[k] += s * x[k];
 }
 
 __global__ void __launch_bounds__(256) k_fill_i32(int32_t* __restrict__ p, int32_t value, int count)
@@ -204,14 +182,6 @@ hipError_t launch_merge_integrate(bool f64, const double* partial, int splits, i
     return hipGetLastError();
 }
 
-hipError_t launch_sum_partials(const double* partial, int splits, int n, double* out, double scale,
-                               int accumulate, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_sum_partials, grid_for(n), dim3(256), 0, st, partial, splits, n, out,
-                       scale, accumulate);
-    return hipGetLastError();
-}
-
 hipError_t launch_pack_f32(const double* v, float4* out, int n, hipStream_t st)
 {
     hipLaunchKernelGGL((k_pack<float4>), grid_for(n), dim3(256), 0, st, v, out, n);
@@ -221,12 +191,6 @@ hipError_t launch_pack_f32(const double* v, float4* out, int n, hipStream_t st)
 hipError_t launch_pack_f64(const double* v, double4* out, int n, hipStream_t st)
 {
     hipLaunchKernelGGL((k_pack<double4>), grid_for(n), dim3(256), 0, st, v, out, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_axpy(double s, const double* x, double* y, int64_t m, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_axpy, grid_for(m), dim3(256), 0, st, s, x, y, m);
     return hipGetLastError();
 }
 

@@ -7,8 +7,8 @@
 namespace sd {
 
 // The current device's counters (defined beside the product kernels in
-// mobility.hip): PREMISE_SLOTS cache lines of [0] pairs with 0 < r < 2a and [1]
-// with r = 0, to be added up.  Work-groups take the slots in turn, since atomics
+// mobility.hip): PREMISE_SLOTS slots of 64 bytes, each [0] pairs with 0 < r < 2a and
+// [1] with r = 0, to be added up.  Work-groups take the slots in turn, since atomics
 // on one address serialise: microseconds with one slot -> this: products of N =
 // 3000 with 0.6 near partners per particle 18.6 -> 14.9 (5000 30.5 -> 27.8), the
 // fold of N = 65536 with 0.4 85 -> 73.

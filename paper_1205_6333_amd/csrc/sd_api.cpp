@@ -374,8 +374,8 @@ PairConst pair_const(const sd_params* p)
     return make_pair_const(p->a, p->eta, p->tensor, p->overlap, box_side(p));
 }
 
-// Launch the pair kernel for n particles; returns the number of splits used
-// through *splits_out.  partial is sized by the caller via partial_bytes().
+// Launch the pair kernel for n particles (see sd_host.h).  partial is sized by the
+// caller via partial_bytes().
 sd_status run_pair(const sd_params* p, int64_t n, const void* pos, const void* frc,
                    const double* x64, int32_t prec, double* partial, const PairLaunch& L,
                    hipStream_t st, double* vel, bool* merged)

@@ -14,12 +14,11 @@ constexpr int64_t MAX_N = (int64_t(1) << 30);
 enum {
     WS_PARTIAL = 0,   // split partials of the pair kernels
     WS_STAGE,         // FP32 / FP64 staged positions of the time loop (two copies)
-    WS_STEP_X,        // positions of every other step (variant 4)
+    WS_STEP_X,        // positions of every other step (variants 2 and 4)
     WS_ADJ_PARTIAL,   // split partials of the adjoint kernel
     WS_ADJ_PACK,      // packed cotangent
     WS_ADJ_REC,       // position records of one checkpoint segment
     WS_ADJ_TRAJ,      // recomputed trajectory of one checkpoint segment
-    WS_ADJ_LAM,       // adjoint state
     WS_ADJ_CKPT,      // checkpoints when the caller passes none
     WS_TUNE,          // autotuner scratch
     WS_LUB,           // lubrication cell list
@@ -63,9 +62,8 @@ bool sym_fits(int64_t n, int block);
 // / 29.6; FP64: N = 3500 18.8 / 22.5, 4000 23.8 / 23.6, 5000 34.3 / 30.4.
 // Microseconds per product, wave- / block-symmetric (compensated): N = 12000
 // 77.5 / -, 16384 125.4 / 121.6 (with 0.4 near partners per particle 136.7 /
-// 154.1), 24576 301 / 243.  FP64,
-// wave-symmetric / one-sided: N = 6000 39.7 / 72.6, 16384 199 / 301, 40000 1107
-// / 1730.
+// 154.1), 24576 301 / 243.  FP64, wave-symmetric / one-sided: N = 6000 39.7 /
+// 72.6, 16384 199 / 301, 40000 1107 / 1730.
 constexpr int64_t ROW_F32_END_N = 5900;
 constexpr int64_t ROW_F64_END_N = 4000;
 constexpr int64_t ROW_ILP2_MIN_N = 1300;
@@ -109,13 +107,15 @@ sd_status run_step(const sd_params* p, int64_t n, const double* x_in, double* x_
                    int32_t prec, const void* pos, void* pos_next, double* partial,
                    const PairLaunch& L, hipStream_t st);
 
-// A sequence of steps that starts and ends in the caller's x.  Variants 0 to 3
-// work in place; variant 4 alternates between x and a library copy (and between
-// two record arrays), beginning with the copy when the number of steps is odd.
+// A sequence of steps that starts and ends in the caller's x.  Variants 0, 1 and 3
+// work in place; variants 2 and 4 (step_apart) alternate between x and a library
+// copy, and between two record arrays, beginning with the copy when the number of
+// steps is odd: in place their last kernel would write positions and records that
+// its other work-groups still read.
 struct StepBuffers {
     double* partial = nullptr;
     char* pos[2] = { nullptr, nullptr };   // records: of the current positions first
-    double* copy = nullptr;                // variant 4
+    double* copy = nullptr;                // variants 2 and 4
     double* cur = nullptr;                 // the current positions
     double* other = nullptr;               // where the next step puts them
 };

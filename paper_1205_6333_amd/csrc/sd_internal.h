@@ -211,14 +211,9 @@ hipError_t launch_wave_adjoint(const PairLaunch& L, int tensor, bool f64, const 
                                const void* frc, void* lam, const double* x64, int n,
                                const PairConst& pc, void* ws, double* lam64, double dt,
                                double* gpos, double* gforce, hipStream_t st);
-// out[3i+k] = sum_s partial (no self term); accumulate != 0 adds scale*sum to out.
-hipError_t launch_sum_partials(const double* partial, int splits, int n, double* out, double scale,
-                               int accumulate, hipStream_t st);
 // f64[3n] -> f32x4 / f64x4 (w = 0)
 hipError_t launch_pack_f32(const double* v, float4* out, int n, hipStream_t st);
 hipError_t launch_pack_f64(const double* v, double4* out, int n, hipStream_t st);
-// y[k] += s * x[k], k < m
-hipError_t launch_axpy(double s, const double* x, double* y, int64_t m, hipStream_t st);
 
 // Batched clusters.
 struct BatchDev {

@@ -7,9 +7,9 @@
 namespace sd {
 
 // Sum of the partials of a particle: its j-side partials of the blocks
-// I = J - 1, J - 2, ... (and the antipode), and its split rows.  A work-group takes 32 particles; its eight slices of 32 lanes take every
-// eighth term, each with its loads issued in groups, and the slices are added
-// in order.  Then, by mode: velocities (mu0 F + sum), or a step of the time
+// I = J - 1, J - 2, ... (and the antipode), and its split rows.  A work-group
+// takes 32 particles; its eight slices of 32 lanes take every eighth term, each
+// with its loads issued in groups, and the slices are added in order.  Then, by mode: velocities (mu0 F + sum), or a step of the time
 // loop (as k_merge_integrate); the positions may be updated in place, since
 // the pair kernel has finished with them.
 template <typename V4>
