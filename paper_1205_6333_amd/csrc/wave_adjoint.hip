@@ -123,7 +123,7 @@ __device__ __forceinline__ void adj_pair(const AdjCoef<T>& c, const V3<T>& d, co
 //
 // Bound by the vector ALU: N = 8192 issues 99 vector instructions per unordered pair
 // in FP32, one per 3.4 cycles and SIMD, and in FP64 111, 84 of them FP64, one per 4.3,
-// at a clock of 1.9 GHz under this load.
+// at a clock of 1.9 GHz.
 // One particle per lane: six sums on each side and nine values of i and j fill
 // the registers (two per lane spilled and gained nothing).  Three waves per
 // SIMD: the bound of four spilled 40 registers and was 3 % slower in FP64, 4 %

@@ -122,7 +122,7 @@ __device__ __forceinline__ void store_sums(const double* si, int n, int ib, int 
 // Bound by the vector ALU: 1321 instructions for the 32 pairs (64 interactions)
 // of a lane and chunk; with the diagonal blocks and what surrounds the chunk 42 per
 // unordered pair at N = 8192, one per 3.8 cycles and SIMD (6007 4.3, 12000 3.5) at a
-// clock of 1.9 GHz under this load.  The chunk pins 103 of the 128 registers that
+// clock of 1.9 GHz.  The chunk pins 103 of the 128 registers that
 // four waves per SIMD leave, and the compiler spills what is left beside it: 18
 // values (76 bytes per lane) for the RPY tensor, 6 for Oseen, four of them reloaded
 // in every chunk, the others on the near branch.  Microseconds per product with the

@@ -41,8 +41,8 @@ __device__ __forceinline__ void pair_sums(WaveI64& L, double A, double Bt, doubl
 //
 // Bound by the FP64 vector ALU: N = 16384 issues 45 vector instructions per unordered
 // pair (two interactions), 39 of them FP64 (one v_rsq_f64, and per two pairs the
-// hand-over of three sums), one per 4.4 cycles and SIMD at a clock of 1.9 GHz under
-// this load; the one-sided kernel spends as much on one interaction.  N =
+// hand-over of three sums), one per 4.4 cycles and SIMD at clocks of 1.9 to 2.1 GHz;
+// the one-sided kernel spends as much on one interaction.  N =
 // 16384: 200 us per product with the fold (1.34 T interactions/s), one-sided
 // kernel and merge 301 us.  Near pairs only set a bit in the hot loop and are
 // evaluated after the chunk's steps: inlined in every step the branch took all

@@ -11,9 +11,12 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PRELUDE = r"""
-import ctypes as C, os, sys
-sys.path.insert(0, %r)
-from paper_1205_6333_amd.binding import SdParams, SdKernelConfig
+import ctypes as C
+class SdParams(C.Structure):         # as in sd.h
+    _fields_ = [("a", C.c_double), ("eta", C.c_double), ("tensor", C.c_int32),
+                ("overlap", C.c_int32), ("box", C.c_double * 3)]
+class SdKernelConfig(C.Structure):
+    _fields_ = [(k, C.c_int32) for k in ("variant", "block", "splits", "ilp", "kahan_block")]
 L = C.CDLL(%r)
 L.stub_log.restype = C.c_char_p
 L.stub_largest.restype = C.c_size_t
@@ -83,7 +86,7 @@ def build() -> str:
 
 def child(lib, script) -> str:
     """Runs script after PRELUDE in a child process; returns what it printed."""
-    r = subprocess.run([sys.executable, "-c", PRELUDE % (ROOT, lib) + script],
+    r = subprocess.run([sys.executable, "-c", PRELUDE % lib + script],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert r.returncode == 0, "exit status %d\n%s" % (r.returncode, r.stdout[-3000:])
     return r.stdout
